@@ -2497,8 +2497,14 @@ extern "C" hipError_t lme_internal_launch_mc(int R, const lme::McArgs *a, int gr
 extern "C" hipError_t lme_internal_launch_mc_average(const double *ex_traj, double *expect,
                                                      int n_traj, int per, hipStream_t s);
 
+extern "C" int lme_internal_mc_reg_rows();
+extern "C" int lme_internal_mc_reg_threads();
+extern "C" hipError_t lme_internal_launch_mc_reg(int R, int as, const lme::McArgs *a, int grid,
+                                                 int lds, hipStream_t s);
+
 struct lme_mc_ctx {
   int n = 0, wo = 0, nc = 0, wc = 0, ne = 0, we = 0;
+  int astruct = -1;   // A: 0 all real, 1 imaginary off-diagonal, 2 real off-diagonal, -1 other
   lme::McLayout L;
   std::vector<uint8_t> tabs;   // operator tables (layout lme::mc_layout), host image
   int device = 0, lds_limit = 0, n_cu = 0;
@@ -2554,6 +2560,14 @@ static int mc_create_impl(const lme_csr *H, int32_t n_c, const lme_csr *C, int32
   if (!h) return fail(LME_ENOMEM, "out of host memory");
   h->n = n;
   h->wo = A.width_offdiag();
+  bool d_real = true, od_real = true, od_imag = true;
+  for (int i = 0; i < n; ++i)
+    for (auto &e : A.rows[i]) {
+      if (e.first == i) d_real = d_real && e.second.imag() == 0.0;
+      if (e.first != i) od_real = od_real && e.second.imag() == 0.0;
+      if (e.first != i) od_imag = od_imag && e.second.real() == 0.0;
+    }
+  h->astruct = od_real && d_real ? 0 : od_imag ? 1 : od_real ? 2 : -1;
   h->nc = n_c;
   h->ne = n_e;
   for (auto &c : Cs) h->wc = std::max(h->wc, c.width());
@@ -2611,7 +2625,40 @@ extern "C" void lme_mc_destroy(lme_mc_handle h) { delete h; }
 // each (R a compiled row count, G * P within the kernel's largest workgroup),
 // about five rows per thread; P trajectories per workgroup, bounded by LDS,
 // enough workgroups for every CU when the trajectories allow it.
-static int mc_plan(const lme_mc_ctx *h, int n_traj, int *R, int *G, int *P) {
+//
+// With at most two off-diagonal entries a row, all real or all imaginary, the
+// kernel with A in registers runs instead (*reg; the general kernel is bound
+// by reading the tables: 98.9 ms against 37.4 ms for 1000 trajectories x 1000
+// steps at n = 4913).  Its workgroup holds up to 512 threads and ten rows a
+// thread (n <= 5120; LDS allows 5090); of the shapes that fit, the one with
+// the least estimated time per product is taken: rounds of workgroups over
+// the CUs, times a fixed latency (barrier and dependent LDS reads, about 600
+// cycles) plus the issue and LDS time of the rows.
+static int mc_plan(const lme_mc_ctx *h, int n_traj, int *R, int *G, int *P, bool *reg) {
+  *reg = false;
+  if (h->wo <= 2 && h->astruct >= 0) {
+    const int maxT = lme_internal_mc_reg_threads();
+    double best = 0.0;
+    for (int r = lme_internal_mc_reg_rows(); r >= 1; --r) {
+      int g = 1;
+      while (g * r < h->n) g <<= 1;
+      if ((r - 1) * g >= h->n) continue;   // fewer rows a thread would do
+      for (int p = 1; p * g <= maxT; p <<= 1) {
+        if (lme_internal_mc_lds_bytes(p * g, p, h->n) > h->lds_limit) break;
+        const int wgs = (n_traj + p - 1) / p, waves = (p * g + 63) / 64;
+        const double rounds = std::ceil((double)wgs / std::max(1, h->n_cu));
+        const double cost = rounds * (600.0 + 40.0 * r + 28.0 * waves * r);
+        if (!*reg || cost < best) {
+          best = cost;
+          *R = r;
+          *G = g;
+          *P = p;
+          *reg = true;
+        }
+      }
+    }
+    if (*reg) return LME_OK;
+  }
   int rows[32], maxT[32];
   const int nr = lme_internal_mc_rows(rows, maxT, 32);
   const int n = h->n;
@@ -2669,7 +2716,8 @@ static int mc_evolve_impl(lme_mc_handle h, int32_t n_t, const double *tlist, int
   // validation done: from here on the device is used
   if ((rc = mc_ensure_device(h))) return rc;
   int R = 0, G = 0, P = 0;
-  if ((rc = mc_plan(h, n_traj, &R, &G, &P))) return rc;
+  bool reg = false;
+  if ((rc = mc_plan(h, n_traj, &R, &G, &P, &reg))) return rc;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   if (out_step != h->out_key || !h->d_out.p) {
     if ((rc = h->d_out.upload(out_step.data(), out_step.size() * sizeof(int32_t), "output steps")))
@@ -2732,7 +2780,8 @@ static int mc_evolve_impl(lme_mc_handle h, int32_t n_t, const double *tlist, int
   a.status = status_dev;
   a.vbuf = static_cast<double *>(h->d_vbuf.p);
   const int lds = lme_internal_mc_lds_bytes(P * G, P, h->n);
-  hipError_t e = lme_internal_launch_mc(R, &a, grid, lds, s);
+  hipError_t e = reg ? lme_internal_launch_mc_reg(R, h->astruct, &a, grid, lds, s)
+                     : lme_internal_launch_mc(R, &a, grid, lds, s);
   if (e != hipSuccess) return hip_fail(e, "launch Monte-Carlo kernel");
   if (expect_dev && per > 0) {
     e = lme_internal_launch_mc_average(ex_traj, static_cast<double *>(expect_dev), n_traj,
