@@ -35,6 +35,9 @@ extern "C" int lme_internal_rk4_configs(int *T, int *EPT, int cap);
 extern "C" int lme_internal_pack_lds_bytes(int n, int m, int blob_bytes, int nb);
 extern "C" int lme_internal_blob_stride(int blob_bytes);
 extern "C" int lme_internal_lane_fits(int wo, int nb, int wb, int nc, int wc);
+extern "C" hipError_t lme_internal_launch_rk4_band(int cfg, int nw, int nc, const lme::Rk4Args *a,
+                                                   int n_packs, int threads, int lds,
+                                                   hipStream_t s);
 extern "C" hipError_t lme_internal_launch_rk4_lane(const lme::Rk4Args *a, int n_packs, int lds,
                                                    hipStream_t s);
 extern "C" hipError_t lme_internal_launch_rk4(int T, int EPT, const lme::Rk4Args *a,
@@ -267,6 +270,8 @@ struct lme_ctx {
   // superoperator form (assembled on first use from the folded operators)
   std::vector<Sparse> A_host;
   std::vector<std::vector<Sparse>> C_host;
+  bool band = false;      // band_structure(), found at create
+  int32_t band_off[lme::kColNC] = {0, 0, 0};
   DevBuf d_sd, d_scol, d_sval;
   int apply_cap = 4096;   // elements per pack of the LDS-staged application
   int apply_lds_kb = 0;   // LDS budget per column-application workgroup (0: device)
@@ -396,6 +401,7 @@ extern "C" void lme_default_options(lme_options *opt) {
 extern "C" const char *lme_last_error(void) { return g_err.c_str(); }
 
 static int ensure_device(lme_ctx *h);
+static bool band_structure(lme_ctx *h);
 
 static int create_impl(int32_t n_inst, const lme_instance *inst, int32_t n_ctrl, int32_t n_e,
                        const lme_segments *seg, const double *u_host, lme_handle *out) {
@@ -529,6 +535,7 @@ static int create_impl(int32_t n_inst, const lme_instance *inst, int32_t n_ctrl,
     h->state_elems += (int64_t)n * n;
   }
 
+  h->band = band_structure(h);
   h->ops.swap(ops);
   h->adj.swap(adj);
   h->eops.swap(eops);
@@ -654,7 +661,8 @@ static int ensure_device(lme_ctx *h) {
 // column) and m (instances per pack) with m*n*G <= T and ceil(n/G) <= EPT,
 // maximising the fraction of the workgroup's T*ept element slots in use.
 // Hermitian column layout (column == 2): the same with n/2 + 1 rows per
-// column.  Column application (column == 3): as column == 1.
+// column.  Column application (column == 3): as column == 1.  Band kernel
+// (column == 4): as column == 2, with the LDS of band_lds_bytes().
 // LDS operator data per instance: the op blob (row and column RK4 kernels),
 // one record per operator row (column application, Hermitian kernel) or
 // nothing (Hermitian kernel with real structure and no control terms: its
@@ -705,13 +713,22 @@ static int plan_packs(lme_ctx *h, int T, int EPT, int adjoint, int cap, int colu
   // LDS of a pack of m instances (the adaptive kernel adds its step control)
   // dp: 1 adaptive kernel (step control), 2 gradient kernel (sums)
   auto pack_lds = [&](int n, int m, int blob, int nb) {
+    if (column == 4) return lme::band_lds_bytes(n, m);
     return lme_internal_pack_lds_bytes(n, m, blob, nb) +
            (dp == 1 ? lme_internal_dp5_extra_lds(m) : dp == 2 ? lme::align16(8 * m) : 0);
   };
+  // band kernel: a batch of few instances per CU is spread over the CUs, with
+  // fewer diagonals per thread, rather than packed (64 JC of n = 10 to 40,
+  // 1000 steps: 2.0 ms against 2.7)
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess)
+    cus = 0;
+  const int spread = column == 4 && cus > 0 ? std::max(1, (h->n_inst + cus - 1) / cus) : h->n_inst;
   for (auto &g : groups) {
     const InstDesc &d0 = h->inst[g.second[0]];
     const lme::Signature &s = adjoint == 1 ? d0.adj : d0.fwd;
-    const int blob = column == 2 && lme::herm_slots(real_structure(h), s.wo, s.nc, s.nb) ? 0
+    const int blob = column == 4 ? 0
+                     : column == 2 && lme::herm_slots(real_structure(h), s.wo, s.nc, s.nb) ? 0
                      : column >= 2 ? s.n * lme::rec_bytes(s.wo, s.nc, s.nb)
                      : adjoint == 1 ? d0.adj_bytes
                      : adjoint == 2 ? d0.fwd_bytes + d0.adj_bytes : d0.fwd_bytes;
@@ -736,14 +753,14 @@ static int plan_packs(lme_ctx *h, int T, int EPT, int adjoint, int cap, int colu
       return (r > 0 || budget == h->lds_limit) ? r : lds_fit_in(std::min<int64_t>(m, 1), h->lds_limit);
     };
     int m_max = 0, G = 0;
-    const int R = column == 2 ? n / 2 + 1 : n;  // rows per column
+    const int R = column == 2 || column == 4 ? n / 2 + 1 : n;  // rows per column
     if (!column) {
       m_max = lds_fit(std::max<int64_t>(1, cap / n2));  // an instance larger than cap: alone
     } else {
       double best = -1.0;
       for (int gg = (R + EPT - 1) / EPT; gg <= R && gg * n <= T; ++gg) {
         const int ept = (R + gg - 1) / gg;
-        const int m = lds_fit(std::min<int64_t>(T / (gg * n), cnt));
+        const int m = lds_fit(std::min<int64_t>(T / (gg * n), std::min(cnt, spread)));
         if (m < 1) continue;
         const double eff = (double)m * n * R / ((double)ept * T);
         if (eff > best + 1e-12) {
@@ -801,10 +818,7 @@ static int plan_packs(lme_ctx *h, int T, int EPT, int adjoint, int cap, int colu
   // in that schedule holds several instances and half of them fit more
   // threads per column (fewer rows per thread), split it in two.  Packing
   // changes no result bit.
-  int cus = 0;
-  if (column >= 1 && column <= 2 &&
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) == hipSuccess &&
-      cus > 0) {
+  if ((column == 1 || column == 2 || column == 4) && cus > 0) {
     for (int iter = 0; iter < 4 * cus; ++iter) {
       std::priority_queue<std::pair<int64_t, int>, std::vector<std::pair<int64_t, int>>,
                           std::greater<std::pair<int64_t, int>>> free_at;
@@ -824,7 +838,7 @@ static int plan_packs(lme_ctx *h, int T, int EPT, int adjoint, int cap, int colu
       if (last < 0) break;
       PackDesc pk = p->packs[last];
       if (pk.m < 2) break;
-      const int R = column == 2 ? pk.n / 2 + 1 : pk.n;
+      const int R = column == 2 || column == 4 ? pk.n / 2 + 1 : pk.n;
       const int m1 = (pk.m + 1) / 2, m2 = pk.m - m1;
       const int G1 = std::min(R, T / (m1 * pk.n));
       const int ept1 = (R + G1 - 1) / G1;
@@ -845,7 +859,7 @@ static int plan_packs(lme_ctx *h, int T, int EPT, int adjoint, int cap, int colu
       longest_first();
     }
     for (const PackDesc &q : p->packs) {  // what the column kernels assume
-      const int R = column == 2 ? q.n / 2 + 1 : q.n;
+      const int R = column == 2 || column == 4 ? q.n / 2 + 1 : q.n;
       if (q.m < 1 || (int64_t)q.m * q.n * q.G > T || q.G > R || q.ept > EPT ||
           q.ept != (R + q.G - 1) / q.G)
         return fail(LME_EINVAL, "internal: inconsistent pack (n %d, m %d, G %d, rows %d)", q.n,
@@ -1038,6 +1052,34 @@ static int real_structure(const lme_ctx *h) {
     if ((d.flags & (lme::kJumpsReal | lme::kOffdiagImag)) != (lme::kJumpsReal | lme::kOffdiagImag))
       return 0;
   return 1;
+}
+
+// Can the batch use the band kernel?  Real structure, no control terms, the
+// off-diagonal entries of A next to the diagonal, one to kColNC collapse
+// operators with all entries of the k-th on one diagonal, the same one in
+// every instance (an instance with an empty k-th operator fits any), and
+// kBandMinN <= n <= 255.
+static bool band_structure(lme_ctx *h) {
+  if (!real_structure(h)) return false;
+  const int nc = h->inst[0].fwd.nc;
+  if (nc < 1 || nc > lme::kColNC || h->n_ctrl > 0) return false;
+  bool set[lme::kColNC] = {};
+  for (int b = 0; b < h->n_inst; ++b) {
+    const InstDesc &d = h->inst[b];
+    if (d.fwd.nc != nc || d.fwd.wc != 1 || d.fwd.wo > 2 || d.n < lme::kBandMinN || d.n > 255)
+      return false;
+    for (int i = 0; i < d.n; ++i)
+      for (auto &e : h->A_host[b].rows[i])
+        if (std::abs(e.first - i) > 1) return false;
+    for (int k = 0; k < nc; ++k)
+      for (int i = 0; i < d.n; ++i)
+        for (auto &e : h->C_host[b][k].rows[i]) {
+          if (!set[k]) h->band_off[k] = e.first - i;
+          set[k] = true;
+          if (e.first - i != h->band_off[k]) return false;
+        }
+  }
+  return true;
 }
 
 static bool column_fits(const lme_ctx *h, int T, int EPT, bool herm) {
@@ -1531,6 +1573,22 @@ static int evolve_impl(lme_handle h, const lme_options *opt, int32_t n_t, const 
       }
     }
   }
+  // Hermitian states under banded operators: the band kernel wherever it
+  // applies (1000 steps, ms, band kernel / column == 2: 4096 JC of n = 10 to
+  // 80 36.6 / 43.8, one of n = 20 1.08 / 1.97, one of n = 80 5.8 / 5.9; 1024
+  // thermal JC of n = 32 5.3 / 10.9; 1024 Kerr of n = 41 7.7 / 19.3), its
+  // 768-thread configuration first (three wavefronts a SIMD: 36.6 against
+  // 42.1 for 512 threads of 7 diagonals, 38.0 for 1024 of 4, which spill)
+  if (column == 2 && h->band)
+    for (int cc = 1; cc >= 0 && column == 2; --cc) {
+      const int bT = lme::kBandCfg[cc][0], bE = lme::kBandCfg[cc][1];
+      if ((opt->block == 0 || opt->block == bT) && column_fits(h, bT, bE, true)) {
+        T = bT;
+        EPT = bE;
+        column = 4;
+        col_cfg = cc;
+      }
+    }
   bool streamed = opt->path == LME_PATH_STREAMED;
   if (!column && !streamed) {
     if (opt->layout == LME_LAYOUT_COLUMN)
@@ -1608,7 +1666,14 @@ static int evolve_impl(lme_handle h, const lme_options *opt, int32_t n_t, const 
   bool lane = !column && T == 64 && EPT == 1;
   for (auto &d : h->inst)
     lane = lane && lme_internal_lane_fits(d.fwd.wo, d.fwd.nb, d.fwd.wb, d.fwd.nc, d.fwd.wc);
-  if (column)
+  if (column == 4) {
+    std::memcpy(a.band_off, h->band_off, sizeof a.band_off);
+    int threads = 64, nw = 1;
+    for (const PackDesc &q : plan->packs) threads = std::max(threads, (q.m * q.n * q.G + 63) & ~63);
+    for (auto &d : h->inst) nw = std::max(nw, d.fwd.wo);
+    e = lme_internal_launch_rk4_band(col_cfg, nw, nc, &a, (int)plan->packs.size(), threads,
+                                     plan->max_lds, s);
+  } else if (column)
     e = lme_internal_launch_rk4_colown(col_cfg, column == 2, wo, nc, nb, re, &a,
                                        (int)plan->packs.size(), plan->max_lds, s);
   else if (lane)
@@ -2829,6 +2894,8 @@ static std::unique_ptr<lme_ctx> make_replica(const lme_ctx *h, const std::vector
   r->n_ctrl = h->n_ctrl;
   r->n_e = h->n_e;
   r->n_seg = 0;
+  r->band = h->band;
+  std::memcpy(r->band_off, h->band_off, sizeof r->band_off);
   r->ops = h->ops;
   r->adj = h->adj;
   r->eops = h->eops;

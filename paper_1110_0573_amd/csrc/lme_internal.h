@@ -124,6 +124,19 @@ LME_HD constexpr bool herm_slots(bool re, int32_t wo, int32_t nc, int32_t nb) {
   return re && nb == 0 && wo + nc <= 3;
 }
 
+// Band kernel (lme_band.hip): LDS of one buffer of m instances, diagonals -1
+// to n/2 + 1 as rows of n elements; diagonals past the last that a pack's
+// threads may read (with zero coefficients) after the second buffer.
+constexpr int kBandSlack = 8;
+constexpr int kBandMinN = 4;
+// (threads per workgroup, diagonals per thread), by kHermCfg's blocks
+constexpr int kBandCfg[2][2] = {{512, 7}, {768, 5}};
+LME_HD inline int32_t band_rows(int32_t n) { return n / 2 + 3; }
+LME_HD inline int32_t band_buffer_bytes(int32_t n, int32_t m) { return 16 * m * band_rows(n) * n; }
+LME_HD inline int32_t band_lds_bytes(int32_t n, int32_t m) {
+  return 2 * band_buffer_bytes(n, m) + 16 * n * kBandSlack + align16(8 * m) + align16(4 * m);
+}
+
 // Row records of the column-owner kernels (one per operator row, in LDS):
 // 1 + wo + nc + nb*kColWB int32 byte offsets, padded to 16 bytes, then
 // 1 + wo + nc + nb*(1 + kColWB) complex coefficients; the record is an odd
@@ -159,6 +172,7 @@ struct Rk4Args {
   double *expect;           // [n_inst][n_e][n_t]
   int64_t *counts;          // [n_inst][2]
   int32_t *status;          // [n_inst]
+  int32_t band_off[kColNC]; // band kernel: the diagonal of each collapse operator
 };
 
 // Closed-form amplitude c0 + c1 t + c2 t^2 + c3 t^3 + a cos(w t + phi) with
