@@ -39,7 +39,7 @@ extern "C" hipError_t lme_internal_launch_rk4_band(int cfg, int nw, int nc, cons
                                                    int n_packs, int threads, int lds,
                                                    hipStream_t s);
 extern "C" hipError_t lme_internal_launch_rk4_lane(const lme::Rk4Args *a, int n_packs, int lds,
-                                                   hipStream_t s);
+                                                   int quad, hipStream_t s);
 extern "C" hipError_t lme_internal_launch_rk4(int T, int EPT, const lme::Rk4Args *a,
                                               int n_packs, int lds, hipStream_t s);
 extern "C" hipError_t lme_internal_launch_rk4_colown(int cfg, int herm, int wo, int nc, int nb,
@@ -1664,8 +1664,11 @@ static int evolve_impl(lme_handle h, const lme_options *opt, int32_t n_t, const 
   // one-wavefront packs of small instances: one element per lane, the stage
   // input exchanged between lanes
   bool lane = !column && T == 64 && EPT == 1;
-  for (auto &d : h->inst)
+  bool quad = true;   // two-level instances, monomial collapse operators
+  for (auto &d : h->inst) {
     lane = lane && lme_internal_lane_fits(d.fwd.wo, d.fwd.nb, d.fwd.wb, d.fwd.nc, d.fwd.wc);
+    quad = quad && d.n == 2 && d.fwd.wc <= 1;
+  }
   if (column == 4) {
     std::memcpy(a.band_off, h->band_off, sizeof a.band_off);
     int threads = 64, nw = 1;
@@ -1677,7 +1680,7 @@ static int evolve_impl(lme_handle h, const lme_options *opt, int32_t n_t, const 
     e = lme_internal_launch_rk4_colown(col_cfg, column == 2, wo, nc, nb, re, &a,
                                        (int)plan->packs.size(), plan->max_lds, s);
   else if (lane)
-    e = lme_internal_launch_rk4_lane(&a, (int)plan->packs.size(), plan->max_lds, s);
+    e = lme_internal_launch_rk4_lane(&a, (int)plan->packs.size(), plan->max_lds, quad, s);
   else
     e = lme_internal_launch_rk4(T, EPT, &a, (int)plan->packs.size(), plan->max_lds, s);
   if (e != hipSuccess) return hip_fail(e, "launch resident RK4");

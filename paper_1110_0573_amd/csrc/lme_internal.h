@@ -177,11 +177,16 @@ struct Rk4Args {
 
 // Closed-form amplitude c0 + c1 t + c2 t^2 + c3 t^3 + a cos(w t + phi) with
 // p = (c0, c1, c2, c3, a, w, phi).
+// Every product is fused into its sum explicitly: left to the compiler, two
+// kernels evaluating the same amplitude could round it differently.
+LME_HD inline double coeff_poly_at(const double *p, double t) {
+  return fma(t, fma(t, fma(t, p[3], p[2]), p[1]), p[0]) + 0.0;
+}
 LME_HD inline double coeff_fn_at(const double *p, double t) {
   // without a cosine term the polynomial alone (the cosine's product with a
   // zero amplitude could only change the sign of a zero result)
-  const double poly = p[0] + t * (p[1] + t * (p[2] + t * p[3]));
-  return p[4] != 0.0 ? poly + p[4] * cos(p[5] * t + p[6]) : poly + 0.0;
+  return p[4] != 0.0 ? fma(p[4], cos(fma(p[5], t, p[6])), coeff_poly_at(p, t))
+                     : coeff_poly_at(p, t);
 }
 
 // Monte-Carlo wave-function kernel (lme_mc.hip).  Operators of one system:

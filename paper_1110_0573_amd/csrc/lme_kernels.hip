@@ -11,6 +11,8 @@
 // the stage input y, which the resident kernels keep in LDS.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "lme_device.h"
 #include "lme_internal.h"
 
@@ -331,6 +333,58 @@ __device__ __forceinline__ double2 lane_read(double2 v, int src) {
   return make_double2(__shfl(v.x, src, 64), __shfl(v.y, src, 64));
 }
 
+// Expectation values of a one-wavefront pack of small instances (n <= 8), one
+// (instance, operator) pair per lane: write_outputs() takes a wavefront per
+// pair, one after another (64 pairs of a Landau-Zener pack, most of a run
+// with an output every 20 steps).  A lane adds its rows in the order of the
+// butterfly, so the bits are those of write_outputs().
+struct LaneTask {
+  const int32_t *Ec;
+  const double2 *Ev;
+  double *dst;        // output 0
+  int we, b, id;
+};
+
+__device__ __forceinline__ LaneTask lane_task(const Rk4Args &a, const PackDesc &pk,
+                                              const PackLds &L, int task) {
+  LaneTask t;
+  t.b = task / a.n_e;
+  const int e = task - t.b * a.n_e;
+  t.id = L.ids[t.b];
+  const InstDesc &d = a.inst[t.id];
+  t.we = d.we;
+  const uint8_t *ops = a.eops + d.eops_off;
+  t.Ec = reinterpret_cast<const int32_t *>(ops) + e * d.we * pk.n;
+  t.Ev = reinterpret_cast<const double2 *>(ops + eops_val_offset(pk.n, d.we, a.n_e)) +
+         e * d.we * pk.n;
+  t.dst = a.expect + 2 * ((int64_t)t.id * a.n_e + e) * a.n_t;
+  return t;
+}
+
+// first: the pair of this lane in the first round (looked up once)
+__device__ __forceinline__ void lane_outputs(const Rk4Args &a, const PackDesc &pk,
+                                             const PackLds &L, const LaneTask &first, int k) {
+  const int n = pk.n;
+  for (int task = threadIdx.x; task < pk.m * a.n_e; task += 64) {
+    const LaneTask t = task < 64 ? first : lane_task(a, pk, L, task);
+    const double2 *Y = L.Y + t.b * n * n;
+    double2 p[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      p[i] = make_double2(0.0, 0.0);
+      if (i < n)
+        for (int w = 0; w < t.we; ++w) p[i] = cfma(t.Ev[w * n + i], Y[t.Ec[w * n + i] * n + i], p[i]);
+    }
+#pragma unroll
+    for (int off = 4; off > 0; off >>= 1)
+#pragma unroll
+      for (int i = 0; i < off; ++i) p[i] = cadd(p[i], p[i + off]);
+    t.dst[2 * k] = p[0].x;
+    t.dst[2 * k + 1] = p[0].y;
+    if (!cfinite(p[0]) && a.status) a.status[t.id] = 5;  // LME_ENONFINITE
+  }
+}
+
 __global__ __launch_bounds__(64) void rk4_lane_kernel(Rk4Args a) {
   extern __shared__ __align__(16) uint8_t smem[];
   const PackDesc pk = a.packs[blockIdx.x];
@@ -426,6 +480,8 @@ __global__ __launch_bounds__(64) void rk4_lane_kernel(Rk4Args a) {
   double2 rho = own ? reinterpret_cast<const double2 *>(a.rho0)[L.off[b] + r] : zero;
 
   const bool want_expect = a.expect != nullptr && a.n_e > 0;
+  LaneTask first = {};
+  if (want_expect && tid < pk.m * a.n_e) first = lane_task(a, pk, L, tid);
   int next_out = 0;
   const double h = a.h;
   for (int st = 0;; ++st) {
@@ -439,7 +495,7 @@ __global__ __launch_bounds__(64) void rk4_lane_kernel(Rk4Args a) {
               rho;
       }
       __syncthreads();
-      if (want_expect) write_outputs<64>(a, pk, L, next_out);
+      if (want_expect) lane_outputs(a, pk, L, first, next_out);
       ++next_out;
     }
     if (st == a.nsteps) break;
@@ -516,6 +572,244 @@ __global__ __launch_bounds__(64) void rk4_lane_kernel(Rk4Args a) {
       a.counts[2 * (int64_t)L.ids[bb]] = a.nsteps;
       a.counts[2 * (int64_t)L.ids[bb] + 1] = 0;
     }
+}
+
+// ---------------------------------------------------------------------------
+// The same for two-level instances (n = 2) with monomial collapse operators: an
+// instance is a quad of lanes, element (i, j) in lane 2 i + j, and every
+// source is another lane of the quad at a fixed exclusive-or distance (2: the
+// other row, 1: the other column, 3: both), which is a DPP quad permute, a
+// register move, where rk4_lane_kernel's permutes go through LDS.  A batch of
+// two-level problems has fewer wavefronts than the chip has SIMDs, so the
+// instructions and latencies of one wavefront's stage are its time.  Terms and
+// order are those of lindblad_elem(): the bits are rk4_lane_kernel's.
+// 4096 Landau-Zener problems, 29 980 steps, 1500 outputs: 22.4 ms against
+// 92.4 ms (outputs one pair per wavefront in turn, permutes through LDS);
+// 41.1 ms before the bodies were specialised, with branches in every stage.
+// What bounds it: the dependent chain of a lone wavefront, about 190 VALU
+// instructions and 1.8e3 cycles a step.
+// ---------------------------------------------------------------------------
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0u, (uint32_t)b, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0u, (uint32_t)(b >> 32), CTRL, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+// the value of the quad's lane at exclusive-or distance X
+template <int X>
+__device__ __forceinline__ double2 quad_read(double2 v) {
+  constexpr int ctrl = X == 1 ? 0xB1 : X == 2 ? 0x4E : 0x1B;
+  return make_double2(dpp_move<ctrl>(v.x), dpp_move<ctrl>(v.y));
+}
+
+// All steps of a pack, its blobs staged.  NB control terms; FN: 0 segments, 1
+// closed-form amplitudes without a cosine, 2 with; CO: control terms with
+// off-diagonal entries; NJ >= 0: NJ collapse operators, every source at
+// distance 3 (raising and lowering operators), else any.  What a body does
+// not need is not branched over in its steps: a taken branch costs a lone
+// wavefront about as much as three products.
+template <int NB, int FN, bool CO, int NJ>
+__device__ __forceinline__ void quad_pack(const Rk4Args &a, const PackDesc &pk, const PackLds &L,
+                                          const OpView &op) {
+  constexpr int n = 2, n2 = 4, JT = NJ >= 0 ? NJ : kLaneJ;
+  const int E = pk.m * n2, tid = threadIdx.x;
+
+  // lanes past the pack have zero coefficients
+  const bool own = tid < E;
+  const int b = own ? tid / n2 : 0, r = tid & 3, i = r >> 1, j = r & 1;
+  const double2 zero = make_double2(0.0, 0.0);
+  double2 dsum = zero, ao = zero, bo = zero, qd[NB ? NB : 1], qa[NB ? NB : 1], qb[NB ? NB : 1],
+          jp[JT ? JT : 1];
+  int jx[JT ? JT : 1];         // distance of each jump's source; 4: differs from lane to lane
+  int js[JT ? JT : 1];
+  double cf[NB ? NB : 1][7];
+#pragma unroll
+  for (int q = 0; q < NB; ++q) {
+    qd[q] = qa[q] = qb[q] = zero;
+#pragma unroll
+    for (int k = 0; k < 7; ++k) cf[q][k] = 0.0;
+  }
+  if (own) {
+    dsum = cadd(op.D[i], cconj(op.D[j]));
+    if (pk.wo > 0) {
+      ao = op.Oval[i];
+      bo = op.Oval[j];
+    }
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      qd[q] = cadd(op.DB[q * n + i], cconj(op.DB[q * n + j]));
+      if (CO) {
+        qa[q] = op.OBval[q * n + i];
+        qb[q] = op.OBval[q * n + j];
+      }
+      if (FN > 0) {
+        const double *p = a.fn + 7 * ((int64_t)L.ids[b] * a.n_ctrl + q);
+#pragma unroll
+        for (int k = 0; k < 7; ++k) cf[q][k] = p[k];
+      }
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < JT; ++t) {
+    jp[t] = zero;
+    jx[t] = -1;
+    js[t] = tid;
+    if (t < pk.nc) {
+      int x = 0;
+      if (own) {
+        jp[t] = cmul(op.Jval[t * n + i], cconj(op.Jval[t * n + j]));
+        x = 2 * (op.Jcol[t * n + i] ^ i) + (op.Jcol[t * n + j] ^ j);
+        js[t] = tid ^ x;
+      }
+      const bool used = jp[t].x != 0.0 || jp[t].y != 0.0;
+      jx[t] = 4;
+#pragma unroll
+      for (int c = 3; c >= 0; --c)
+        if (__ballot(used && x != c) == 0) jx[t] = c;
+    }
+  }
+  double2 rho = own ? reinterpret_cast<const double2 *>(a.rho0)[L.off[b] + r] : zero;
+
+  const bool want_expect = a.expect != nullptr && a.n_e > 0;
+  LaneTask first = {};
+  if (want_expect && tid < pk.m * a.n_e) first = lane_task(a, pk, L, tid);
+  int next_out = 0, due = a.out_step[0];
+  const double h = a.h;
+  for (int st = 0;; ++st) {
+    // outputs due after st steps (st = 0: the initial state)
+    while (due == st) {
+      __syncthreads();
+      if (own) {
+        L.Y[tid] = rho;
+        if (a.states)
+          reinterpret_cast<double2 *>(a.states)[(int64_t)next_out * a.state_elems + L.off[b] + r] =
+              rho;
+      }
+      __syncthreads();
+      if (want_expect) lane_outputs(a, pk, L, first, next_out);
+      ++next_out;
+      due = next_out < a.n_t ? a.out_step[next_out] : -1;
+    }
+    if (st == a.nsteps) break;
+
+    // amplitudes: a piecewise-constant segment value for the whole step, or
+    // the closed form at each stage's time (those of rk4_stage_controls())
+    double u[NB ? NB : 1] = {};
+    if (NB && FN == 0) {
+      const int seg = a.seg_of_step[st];
+#pragma unroll
+      for (int q = 0; q < NB; ++q)
+        u[q] = own && seg >= 0 ? a.u[((int64_t)L.ids[b] * a.n_ctrl + q) * a.n_seg + seg] : 0.0;
+    }
+    const double tb = a.t0 + (double)st * h;
+    double2 yn = rho, acc = zero;
+#pragma unroll
+    for (int stage = 0; stage < 4; ++stage) {
+      const double cnext = stage < 2 ? 0.5 * h : (stage == 2 ? h : 0.0);
+      const double wgt = (stage == 0 || stage == 3) ? 1.0 : 2.0;
+      if (FN > 0 && stage != 2) {   // (the third stage is at the second's time)
+        const double ts = stage == 0 ? tb : (stage == 3 ? tb + h : tb + 0.5 * h);
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+          const double *p = cf[q];
+          u[q] = FN == 2 ? coeff_fn_at(p, ts) : coeff_poly_at(p, ts);
+        }
+      }
+      const double2 yr = quad_read<2>(yn), yc = quad_read<1>(yn);
+      // (L y)_ij in the order of lindblad_elem()
+      double2 kv = cmul(dsum, yn);
+      kv = cfma(ao, yr, kv);
+      kv = cfma_conj(bo, yc, kv);
+#pragma unroll
+      for (int q = 0; q < NB; ++q) {
+        double2 tq = cmul(qd[q], yn);
+        if (CO) {
+          tq = cfma(qa[q], yr, tq);
+          tq = cfma_conj(qb[q], yc, tq);
+        }
+        const double2 s = caxpy(u[q], tq, kv);
+        if (u[q] != 0.0) {
+          kv.x = s.x;
+          kv.y = s.y;
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < JT; ++t)
+        if (NJ >= 0 || t < pk.nc) {
+          double2 ys;
+          if (NJ >= 0 || jx[t] == 3) ys = quad_read<3>(yn);
+          else if (jx[t] == 0) ys = yn;
+          else if (jx[t] == 1) ys = yc;
+          else if (jx[t] == 2) ys = yr;
+          else ys = lane_read(yn, js[t]);
+          kv = cfma(jp[t], ys, kv);
+        }
+      acc = caxpy(wgt, kv, acc);
+      yn = caxpy(cnext, kv, rho);
+    }
+    rho = caxpy(h / 6.0, acc, rho);
+  }
+
+  if (a.rho_out && own) reinterpret_cast<double2 *>(a.rho_out)[L.off[b] + r] = rho;
+  if (a.counts)
+    for (int bb = tid; bb < pk.m; bb += 64) {
+      a.counts[2 * (int64_t)L.ids[bb]] = a.nsteps;
+      a.counts[2 * (int64_t)L.ids[bb] + 1] = 0;
+    }
+}
+
+template <int NB>
+__global__ __launch_bounds__(64) void rk4_quad_kernel(Rk4Args a) {
+  extern __shared__ __align__(16) uint8_t smem[];
+  const PackDesc pk = a.packs[blockIdx.x];
+  constexpr int n = 2;
+  const PackLds L = carve(smem, pk);
+  const BlobLayout BL = blob_layout(n, pk.wo, pk.nb, pk.wb, pk.nc, pk.wc);
+  const int tid = threadIdx.x;
+  for (int b = tid; b < pk.m; b += 64) {
+    const int id = a.order[pk.first + b];
+    L.ids[b] = id;
+    L.off[b] = a.inst[id].rho_off;
+    if (a.status) a.status[id] = 0;
+  }
+  stage_blobs(L.blobs, pk, a.order, a.inst, a.ops, 0);
+  __syncthreads();
+  const int b = tid < 4 * pk.m ? tid / 4 : 0;
+  const OpView op = make_view(L.blobs + (size_t)b * pk.blob_stride, BL);
+  // what the pack's instances have in common (the same for every lane)
+  bool flips = pk.nc <= 2;
+  for (int t = 0; t < pk.nc; ++t)
+    for (int q = 0; q < n; ++q) {
+      const double2 v = op.Jval[t * n + q];
+      flips = flips && (op.Jcol[t * n + q] != q || (v.x == 0.0 && v.y == 0.0));
+    }
+  flips = __ballot(!flips) == 0;
+  bool cosine = false;
+  if (a.fn)
+    for (int q = 0; q < NB; ++q)
+      cosine = cosine || a.fn[7 * ((int64_t)L.ids[b] * a.n_ctrl + q) + 4] != 0.0;
+  cosine = __ballot(cosine) != 0;
+  const bool co = pk.wb > 0;
+  auto run = [&](auto fn) __attribute__((always_inline)) {
+    constexpr int F = decltype(fn)::value;
+    if (F == 2 || !flips) {
+      if (co) quad_pack<NB, F, true, -1>(a, pk, L, op);
+      else quad_pack<NB, F, false, -1>(a, pk, L, op);
+    } else if (pk.nc == 0) {
+      if (co) quad_pack<NB, F, true, 0>(a, pk, L, op);
+      else quad_pack<NB, F, false, 0>(a, pk, L, op);
+    } else if (pk.nc == 1) {
+      if (co) quad_pack<NB, F, true, 1>(a, pk, L, op);
+      else quad_pack<NB, F, false, 1>(a, pk, L, op);
+    } else {
+      if (co) quad_pack<NB, F, true, 2>(a, pk, L, op);
+      else quad_pack<NB, F, false, 2>(a, pk, L, op);
+    }
+  };
+  if (!a.fn) run(std::integral_constant<int, 0>{});
+  else if (NB && cosine) run(std::integral_constant<int, NB ? 2 : 0>{});
+  else run(std::integral_constant<int, NB ? 1 : 0>{});
 }
 
 // ---------------------------------------------------------------------------
@@ -3189,12 +3483,20 @@ extern "C" int lme_internal_lane_fits(int wo, int nb, int wb, int nc, int wc) {
          nc * wc * wc <= lme::kLaneJ;
 }
 
+// quad: every instance has n = 2 and at most one entry per row of each
+// collapse operator.
 extern "C" hipError_t lme_internal_launch_rk4_lane(const lme::Rk4Args *a, int n_packs, int lds,
-                                                   hipStream_t s) {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(lme::rk4_lane_kernel),
+                                                   int quad, hipStream_t s) {
+  void (*k)(lme::Rk4Args) = lme::rk4_lane_kernel;
+  if (quad) {
+    k = a->n_ctrl == 0 ? lme::rk4_quad_kernel<0>
+        : a->n_ctrl == 1 ? lme::rk4_quad_kernel<1> : lme::rk4_quad_kernel<2>;
+    if (a->n_ctrl > lme::kLaneNB) return hipErrorInvalidValue;
+  }
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(lme::rk4_lane_kernel, dim3(n_packs), dim3(64), lds, s, *a);
+  hipLaunchKernelGGL(k, dim3(n_packs), dim3(64), lds, s, *a);
   return hipGetLastError();
 }
 
