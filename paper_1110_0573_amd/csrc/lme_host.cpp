@@ -63,6 +63,11 @@ extern "C" hipError_t lme_internal_launch_apply_global(const lme::ApplyGArgs *a,
 extern "C" hipError_t lme_internal_launch_apply_rows(int R, int re, const lme::ApplyGArgs *a,
                                                     int lds, hipStream_t s);
 extern "C" hipError_t lme_internal_launch_superop(const lme::SuperArgs *a, hipStream_t s);
+extern "C" hipError_t lme_internal_launch_apply_flip(int logn, const lme::FlipArgs *f,
+                                                     const double *y, double *out, hipStream_t s);
+extern "C" hipError_t lme_internal_sdp_flip_prepare(int logn);
+extern "C" hipError_t lme_internal_launch_sdp_flip(int logn, int s, const lme::FlipArgs *f,
+                                                   const lme::StreamArgs *a, hipStream_t st);
 extern "C" hipError_t lme_internal_sdp_rows_prepare(int re, int lds);
 extern "C" hipError_t lme_internal_launch_sdp_rows(int s, int re, const lme::StreamArgs *a,
                                                    int lds, hipStream_t st);
@@ -267,6 +272,13 @@ struct lme_ctx {
   // streamed steppers: > 0 when their tiles are 16-row blocks (the LDS of
   // the row-block stage kernel)
   int32_t srows_lds = 0;
+  // spin-flip operators (flip_structure(), build_flip()): log2 of the
+  // dimension every instance has, 0: no; the tables of the forward and of the
+  // adjoint operators (host images until they are uploaded)
+  int flip_logn = 0;
+  lme::FlipArgs flip[2];
+  std::vector<double> flip_tab[2];
+  DevBuf d_flip[2];
   // superoperator form (assembled on first use from the folded operators)
   std::vector<Sparse> A_host;
   std::vector<std::vector<Sparse>> C_host;
@@ -402,6 +414,7 @@ extern "C" const char *lme_last_error(void) { return g_err.c_str(); }
 
 static int ensure_device(lme_ctx *h);
 static bool band_structure(lme_ctx *h);
+static void build_flip(lme_ctx *h);
 
 static int create_impl(int32_t n_inst, const lme_instance *inst, int32_t n_ctrl, int32_t n_e,
                        const lme_segments *seg, const double *u_host, lme_handle *out) {
@@ -536,6 +549,7 @@ static int create_impl(int32_t n_inst, const lme_instance *inst, int32_t n_ctrl,
   }
 
   h->band = band_structure(h);
+  build_flip(h);
   h->ops.swap(ops);
   h->adj.swap(adj);
   h->eops.swap(eops);
@@ -649,6 +663,13 @@ static int ensure_device(lme_ctx *h) {
   if (!h->fn.empty() &&
       (rc = h->d_fn.upload(h->fn.data(), h->fn.size() * sizeof(double), "closed-form amplitudes")))
     return rc;
+  for (int adj = 0; adj < 2 && h->flip_logn > 0; ++adj) {
+    std::vector<double> &tab = h->flip_tab[adj];
+    if ((rc = h->d_flip[adj].upload(tab.data(), tab.size() * sizeof(double), "spin-flip tables")))
+      return rc;
+    h->flip[adj].tab = static_cast<const double *>(h->d_flip[adj].p);
+    std::vector<double>().swap(tab);
+  }
   h->on_device = true;
   return LME_OK;
 }
@@ -1250,12 +1271,18 @@ static int evolve_dp5_streamed(lme_ctx *h, const lme_options *opt, int32_t n_t,
   a.counts = counts_dev;
   a.status = status_dev;
   const int re = real_structure(h);
-  if (h->srows_lds > 0) {
+  const bool flip = h->srows_lds > 0 && h->flip_logn > 0;
+  if (flip) {
+    hipError_t e = lme_internal_sdp_flip_prepare(h->flip_logn);
+    if (e != hipSuccess) return hip_fail(e, "set up the spin-flip stage kernels");
+  } else if (h->srows_lds > 0) {
     hipError_t e = lme_internal_sdp_rows_prepare(re, h->srows_lds);
     if (e != hipSuccess) return hip_fail(e, "set up the row-block stage kernel");
   }
   auto L = [&](int which, int arg, hipStream_t st) -> int {
-    hipError_t e = which == 0 && h->srows_lds > 0
+    hipError_t e = which == 0 && flip
+                       ? lme_internal_launch_sdp_flip(h->flip_logn, arg, &h->flip[0], &a, st)
+                   : which == 0 && h->srows_lds > 0
                        ? lme_internal_launch_sdp_rows(arg, re, &a, h->srows_lds, st)
                        : lme_internal_launch_sdp(which, arg, &a, st);
     return e == hipSuccess ? LME_OK : hip_fail(e, "launch streamed DOPRI5");
@@ -1741,7 +1768,7 @@ static int ensure_tiles(lme_ctx *h) {
   std::vector<lme::Tile> t;
   for (int b = 0; b < h->n_inst; ++b) {
     const int n = h->inst[b].n, n2 = n * n;
-    const int step = h->srows_lds ? 16 * n : kTileElems;
+    const int step = !h->srows_lds ? kTileElems : (h->flip_logn > 0 ? lme::kFlipRows : 16) * n;
     for (int e0 = 0; e0 < n2; e0 += step) {
       lme::Tile x;
       x.inst = b;
@@ -1824,6 +1851,95 @@ static int ensure_row_tiles(lme_ctx *h) {
   return LME_OK;
 }
 
+// Can the batch use the spin-flip kernels?  Real structure, no control terms,
+// every instance of the same dimension 128 or 256, every off-diagonal entry
+// of A in a column i xor 2^b, every collapse operator (the same number in
+// each instance, at most kFlipMaxOps) either diagonal or with all entries at
+// one i xor 2^b, operator k of the same kind in every instance.  Fills
+// kind[k]: the bit, or -1 for a diagonal operator.
+static bool flip_structure(const lme_ctx *h, int *logn, std::vector<int> *kind) {
+  if (!real_structure(h) || h->n_ctrl > 0 || h->A_host.size() != (size_t)h->n_inst) return false;
+  const int n = h->dims[0], nc = (int)h->C_host[0].size();
+  if ((n != 128 && n != 256) || nc > lme::kFlipMaxOps) return false;
+  *logn = n == 256 ? 8 : 7;
+  constexpr int kUnset = -2;
+  kind->assign(nc, kUnset);
+  auto bit_of = [](int x) {   // b for x = 2^b, else -1
+    for (int b = 0; b < 8; ++b)
+      if (x == 1 << b) return b;
+    return -1;
+  };
+  for (int q = 0; q < h->n_inst; ++q) {
+    if (h->dims[q] != n || (int)h->C_host[q].size() != nc) return false;
+    for (int i = 0; i < n; ++i)
+      for (auto &e : h->A_host[q].rows[i])
+        if (e.first != i && bit_of(e.first ^ i) < 0) return false;
+    for (int k = 0; k < nc; ++k)
+      for (int i = 0; i < n; ++i)
+        for (auto &e : h->C_host[q][k].rows[i]) {
+          const int b = e.first == i ? -1 : bit_of(e.first ^ i);
+          if (e.first != i && b < 0) return false;
+          if ((*kind)[k] == kUnset) (*kind)[k] = b;
+          if ((*kind)[k] != b) return false;
+        }
+  }
+  for (int &b : *kind)
+    if (b == kUnset) b = -1;   // an operator without entries
+  return true;
+}
+
+// Builds the host images of the spin-flip tables (create); flip_logn says
+// whether they exist.
+static void build_flip(lme_ctx *h) {
+  int logn = 0;
+  std::vector<int> kind;
+  if (!flip_structure(h, &logn, &kind)) return;
+  const int n = 1 << logn;
+  std::vector<int> flips, diag;
+  lme::FlipArgs f;
+  std::memset(&f, 0, sizeof f);
+  for (int b = 0; b < logn; ++b) {
+    f.first[b] = (int32_t)flips.size();
+    for (size_t k = 0; k < kind.size(); ++k)
+      if (kind[k] == b) flips.push_back((int)k);
+  }
+  for (int b = logn; b < 10; ++b) f.first[b] = (int32_t)flips.size();
+  for (size_t k = 0; k < kind.size(); ++k)
+    if (kind[k] < 0) diag.push_back((int)k);
+  f.nf = (int32_t)flips.size();
+  f.nd = (int32_t)diag.size();
+  f.stride = (int64_t)n * (2 + logn + f.nf + f.nd);
+  f.n_tiles = h->n_inst * (n / lme::kFlipRows);
+  for (int adj = 0; adj < 2; ++adj) {
+    std::vector<double> tab((size_t)f.stride * h->n_inst, 0.0);
+    for (int q = 0; q < h->n_inst; ++q) {
+      double *D = tab.data() + (size_t)q * f.stride, *FA = D + 2 * n, *FJ = FA + logn * n,
+             *Z = FJ + (size_t)f.nf * n;
+      // entry (i, c) of A or C; the adjoint holds its conjugate at (c, i)
+      for (int i = 0; i < n; ++i)
+        for (auto &e : h->A_host[q].rows[i]) {
+          const int c = e.first, row = adj ? c : i;
+          const double im = adj ? -e.second.imag() : e.second.imag();
+          if (c == i) {
+            D[2 * i] = e.second.real();
+            D[2 * i + 1] = im;
+          } else {
+            FA[__builtin_ctz(c ^ i) * n + row] = im;
+          }
+        }
+      for (int k = 0; k < f.nf + f.nd; ++k) {
+        double *T = k < f.nf ? FJ + (size_t)k * n : Z + (size_t)(k - f.nf) * n;
+        const Sparse &C = h->C_host[q][k < f.nf ? flips[k] : diag[k - f.nf]];
+        for (int i = 0; i < n; ++i)
+          for (auto &e : C.rows[i]) T[adj ? e.first : i] = e.second.real();
+      }
+    }
+    h->flip_tab[adj].swap(tab);
+    h->flip[adj] = f;
+  }
+  h->flip_logn = logn;
+}
+
 // Streamed application (stage input and result in HBM).  rows: allow the
 // row-block kernel (every instance 128 <= n <= 1024); otherwise, and for the
 // explicit streamed form, every element gathers straight from memory.
@@ -1880,6 +1996,10 @@ static int apply_streamed(lme_ctx *h, int adjoint, double t, const double *u_dev
   a.seg = ctl.seg;
   a.y = static_cast<const double *>(y_dev);
   a.out = static_cast<double *>(out_dev);
+  if (rows && h->flip_logn > 0) {
+    hipError_t e = lme_internal_launch_apply_flip(h->flip_logn, &h->flip[adjoint], a.y, a.out, s);
+    return e == hipSuccess ? LME_OK : hip_fail(e, "launch spin-flip apply");
+  }
   if (rows) {
     a.tiles = static_cast<const lme::Tile *>(h->d_rtiles.p);
     a.n_tiles = h->n_rtiles;

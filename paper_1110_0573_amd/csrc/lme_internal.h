@@ -362,6 +362,18 @@ struct StreamArgs {
   int32_t *status;
 };
 
+// Spin-flip operators of a batch (lme_flip.hip): per-instance tables and the
+// collapse operators' bits.
+constexpr int kFlipMaxOps = 32;
+constexpr int kFlipRows = 8;      // rows of a tile
+struct FlipArgs {
+  const double *tab;      // instance b at tab + b * stride
+  int64_t stride;         // doubles
+  int32_t n_tiles;        // kFlipRows-row blocks of the batch
+  int32_t nf, nd;         // flipping and diagonal collapse operators
+  int32_t first[10];      // flipping operators of bit b: first[b] .. first[b + 1]
+};
+
 // Per-call arguments of the one-shot Liouvillian application.
 struct ApplyArgs {
   const PackDesc *packs;
