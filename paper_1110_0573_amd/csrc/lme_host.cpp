@@ -35,6 +35,9 @@ extern "C" int lme_internal_rk4_configs(int *T, int *EPT, int cap);
 extern "C" int lme_internal_pack_lds_bytes(int n, int m, int blob_bytes, int nb);
 extern "C" int lme_internal_blob_stride(int blob_bytes);
 extern "C" int lme_internal_lane_fits(int wo, int nb, int wb, int nc, int wc);
+extern "C" hipError_t lme_internal_launch_dp5_band(int cfg, int nw, int nc, const lme::Dp5Args *a,
+                                                   int n_packs, int threads, int lds,
+                                                   hipStream_t s);
 extern "C" hipError_t lme_internal_launch_rk4_band(int cfg, int nw, int nc, const lme::Rk4Args *a,
                                                    int n_packs, int threads, int lds,
                                                    hipStream_t s);
@@ -683,7 +686,8 @@ static int ensure_device(lme_ctx *h) {
 // maximising the fraction of the workgroup's T*ept element slots in use.
 // Hermitian column layout (column == 2): the same with n/2 + 1 rows per
 // column.  Column application (column == 3): as column == 1.  Band kernel
-// (column == 4): as column == 2, with the LDS of band_lds_bytes().
+// (column == 4): as column == 2, with the LDS of band_lds_bytes(); adaptive
+// band kernel (column == 5): as column == 1, with that of band_dp_lds_bytes().
 // LDS operator data per instance: the op blob (row and column RK4 kernels),
 // one record per operator row (column application, Hermitian kernel) or
 // nothing (Hermitian kernel with real structure and no control terms: its
@@ -735,6 +739,7 @@ static int plan_packs(lme_ctx *h, int T, int EPT, int adjoint, int cap, int colu
   // dp: 1 adaptive kernel (step control), 2 gradient kernel (sums)
   auto pack_lds = [&](int n, int m, int blob, int nb) {
     if (column == 4) return lme::band_lds_bytes(n, m);
+    if (column == 5) return lme::band_dp_lds_bytes(n, m, h->inst[0].fwd.nc);
     return lme_internal_pack_lds_bytes(n, m, blob, nb) +
            (dp == 1 ? lme_internal_dp5_extra_lds(m) : dp == 2 ? lme::align16(8 * m) : 0);
   };
@@ -744,11 +749,11 @@ static int plan_packs(lme_ctx *h, int T, int EPT, int adjoint, int cap, int colu
   int cus = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess)
     cus = 0;
-  const int spread = column == 4 && cus > 0 ? std::max(1, (h->n_inst + cus - 1) / cus) : h->n_inst;
+  const int spread = column >= 4 && cus > 0 ? std::max(1, (h->n_inst + cus - 1) / cus) : h->n_inst;
   for (auto &g : groups) {
     const InstDesc &d0 = h->inst[g.second[0]];
     const lme::Signature &s = adjoint == 1 ? d0.adj : d0.fwd;
-    const int blob = column == 4 ? 0
+    const int blob = column >= 4 ? 0
                      : column == 2 && lme::herm_slots(real_structure(h), s.wo, s.nc, s.nb) ? 0
                      : column >= 2 ? s.n * lme::rec_bytes(s.wo, s.nc, s.nb)
                      : adjoint == 1 ? d0.adj_bytes
@@ -839,7 +844,7 @@ static int plan_packs(lme_ctx *h, int T, int EPT, int adjoint, int cap, int colu
   // in that schedule holds several instances and half of them fit more
   // threads per column (fewer rows per thread), split it in two.  Packing
   // changes no result bit.
-  if ((column == 1 || column == 2 || column == 4) && cus > 0) {
+  if (column >= 1 && column != 3 && cus > 0) {
     for (int iter = 0; iter < 4 * cus; ++iter) {
       std::priority_queue<std::pair<int64_t, int>, std::vector<std::pair<int64_t, int>>,
                           std::greater<std::pair<int64_t, int>>> free_at;
@@ -1451,8 +1456,23 @@ static int evolve_dp5(lme_handle h, const lme_options *opt, int32_t n_t, const d
       h->stops_key.swap(key);
     }
   }
+  // banded operators: the band kernel where it holds every instance (n <= 64;
+  // the same bits).  A step of one driven Kerr system, here / column kernel:
+  // n = 15 4.4 / 11.0 us, 31 7.8 / 15.0, 45 13.1 / 27.2, 60 30.1 / 38.5.  The
+  // first configuration serves n <= 48; beyond it a thread needs more
+  // diagonals than 768 threads have registers for.
+  int dcfg = 0;
+  while (dcfg < 2 && !column_fits(h, lme::kBandDpCfg[dcfg][0], lme::kBandDpCfg[dcfg][1], false))
+    ++dcfg;
+  bool band = col_ept && opt->block == 0 && h->band && nb == 0 && dcfg < 2;
+  for (auto &d : h->inst)
+    band = band && lme::band_dp_lds_bytes(d.n, 1, nc) <= h->lds_limit;
   Plan *plan = nullptr;
-  if (col_ept) {
+  if (band) {
+    streamed = false;
+    const int bT = lme::kBandDpCfg[dcfg][0], bE = lme::kBandDpCfg[dcfg][1];
+    if ((rc = plan_packs(h, bT, bE, 0, bT * bE, 5, 1, &plan, 0, !noalloc))) return rc;
+  } else if (col_ept) {
     streamed = false;
     if ((rc = plan_packs(h, col_T(col_ept), col_ept, 0, col_T(col_ept) * col_ept, 1, 1, &plan, 0,
                          !noalloc)))
@@ -1475,7 +1495,7 @@ static int evolve_dp5(lme_handle h, const lme_options *opt, int32_t n_t, const d
     kbuf = reinterpret_cast<double *>(na.base + na.kbuf_off);
   }
 
-  if (!streamed && !noalloc) {
+  if (!streamed && !noalloc && !band) {
     const size_t kbytes = (size_t)7 * h->state_elems * 16;
     if (h->d_kbuf.bytes < kbytes) {
       h->d_kbuf.release();
@@ -1526,6 +1546,14 @@ static int evolve_dp5(lme_handle h, const lme_options *opt, int32_t n_t, const d
   if (streamed)
     return evolve_dp5_streamed(h, opt, n_t, tlist, rho0_dev, u_dev, expect_dev, states_dev,
                                rho_out_dev, counts_dev, status_dev, s, a);
+  if (band) {
+    std::memcpy(a.band_off, h->band_off, sizeof a.band_off);
+    int threads = 64;
+    for (const PackDesc &q : plan->packs) threads = std::max(threads, (q.m * q.n * q.G + 63) & ~63);
+    hipError_t eb = lme_internal_launch_dp5_band(dcfg, wo, nc, &a, (int)plan->packs.size(), threads,
+                                                 plan->max_lds, s);
+    return eb == hipSuccess ? LME_OK : hip_fail(eb, "launch resident DOPRI5");
+  }
   hipError_t e = col_ept ? lme_internal_launch_dp5_col(col_ept, wo, nc, nb, real_structure(h), &a,
                                                        (int)plan->packs.size(), plan->max_lds, s)
                          : lme_internal_launch_dp5(EPT, &a, (int)plan->packs.size(),

@@ -137,6 +137,17 @@ LME_HD inline int32_t band_lds_bytes(int32_t n, int32_t m) {
   return 2 * band_buffer_bytes(n, m) + 16 * n * kBandSlack + align16(8 * m) + align16(4 * m);
 }
 
+// Adaptive band kernel (lme_band_dp5.hip), all n diagonals: one buffer holds
+// those of m instances and two rows past the last (read with zero
+// coefficients); then the row tables (2 n rows of 16 bytes each), step
+// control, 2 m + 2 doubles, offsets and ids.
+// (threads per workgroup, diagonals per thread)
+constexpr int kBandDpCfg[2][2] = {{768, 3}, {512, 8}};
+LME_HD inline int32_t band_dp_buffer_bytes(int32_t n, int32_t m) {
+  return 16 * (m * n + 2) * n;
+}
+LME_HD inline int32_t band_dp_tables(int32_t nc) { return nc > 2 ? 4 : 3; }
+
 // Row records of the column-owner kernels (one per operator row, in LDS):
 // 1 + wo + nc + nb*kColWB int32 byte offsets, padded to 16 bytes, then
 // 1 + wo + nc + nb*(1 + kColWB) complex coefficients; the record is an odd
@@ -236,6 +247,7 @@ struct McArgs {
 
 // Per-call arguments of the resident Dormand-Prince kernel.
 struct Dp5Args {
+  int32_t band_off[kColNC]; // band kernel: the diagonal of each collapse operator
   const PackDesc *packs;
   const int32_t *order;
   const InstDesc *inst;
@@ -326,6 +338,11 @@ struct DpCtl {
   int64_t n_acc, n_rej;
   int32_t stop, status, active, accept, landing, seg, k1_seg, prev_rej, out_due, need_k1;
 };
+
+LME_HD inline int32_t band_dp_lds_bytes(int32_t n, int32_t m, int32_t nc) {
+  return 2 * band_dp_buffer_bytes(n, m) + band_dp_tables(nc) * 32 * m * n +
+         align16(m * (int32_t)sizeof(DpCtl)) + 16 * m + 16 + align16(8 * m) + align16(4 * m);
+}
 
 // Per-call arguments of the streamed steppers (one grid-wide kernel per
 // stage; state and stage data in HBM).
