@@ -16,9 +16,11 @@
 //                         registers, but for its first and last diagonal
 //   y[i][j -+ 1]          diagonal d +- 1, column j -+ 1
 //   y[i + delta][j + delta]   the same diagonal, column j + delta
-// LDS holds the stage input by diagonals, rows of n columns, so every access
-// of a wavefront is contiguous (no bank conflicts) and addressed by a register
-// per operand plus a uniform offset per diagonal.  Besides the owned diagonals
+// LDS holds the stage input by diagonals, rows of n columns, so the lanes of
+// one run of columns access contiguous addresses (1.3 conflict cycles an LDS
+// instruction on the sweep, from wavefronts that span several columns' runs
+// and from wrapped neighbours; 2.1 in rk4_herm_kernel) and each operand is
+// addressed by a register plus a uniform offset per diagonal.  Besides the owned diagonals
 // it holds their neighbours -1 and n/2 + 1 (conjugates of diagonals 1 and
 // n - n/2 - 1, stored by their owners).  Half the matrix leaves room for two
 // buffers: a stage reads one and writes the other, one barrier per stage.

@@ -51,6 +51,22 @@ __constant__ double kDpE[7] = {35.0 / 384 - 5179.0 / 57600, 0.0, 500.0 / 1113 - 
                           125.0 / 192 - 393.0 / 640, -2187.0 / 6784 - (-92097.0 / 339200),
                           11.0 / 84 - 187.0 / 2100, 0.0 - 1.0 / 40};
 
+// Sum over each instance's n2 entries of buf (LDS doubles) -> out[b];
+// waves take instances round-robin, lanes stride the entries, then a
+// butterfly: the order of dp5_resident_kernel's sum.
+__device__ __forceinline__ void per_instance_sum_waves(const double *buf, int m, int n2, double *out,
+                                              int waves) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int b = wave; b < m; b += waves) {
+    double v = 0.0;
+#pragma unroll 8
+    for (int e = lane; e < n2; e += 64) v += buf[b * n2 + e];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    if (lane == 0) out[b] = v;
+  }
+}
+
 struct DpLds {
   uint8_t *buf;        // two buffers
   uint8_t *tab;        // row tables

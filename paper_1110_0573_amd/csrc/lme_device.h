@@ -72,24 +72,4 @@ __device__ __forceinline__ double2 wave_sum(double2 v) {
 // every product here is below 2^24.
 __device__ __forceinline__ int mul24(int a, int b) { return (int)__umul24((unsigned)a, (unsigned)b); }
 
-// Sum over each instance's n2 entries of buf (LDS doubles) -> out[b];
-// waves take instances round-robin, lanes stride the entries, then a
-// butterfly: a fixed order.
-__device__ inline void per_instance_sum_waves(const double *buf, int m, int n2, double *out,
-                                              int waves) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int b = wave; b < m; b += waves) {
-    double v = 0.0;
-#pragma unroll 8
-    for (int e = lane; e < n2; e += 64) v += buf[b * n2 + e];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    if (lane == 0) out[b] = v;
-  }
-}
-template <int T>
-__device__ void per_instance_sum(const double *buf, int m, int n2, double *out) {
-  per_instance_sum_waves(buf, m, n2, out, T / 64);
-}
-
 }  // namespace lme

@@ -1540,6 +1540,21 @@ __host__ __device__ inline int32_t dp_ctl_bytes(int32_t m) {
   return align16(m * (int32_t)sizeof(DpCtl));
 }
 
+// Sum over each instance's n2 entries of buf (LDS doubles) -> out[b];
+// waves take instances round-robin, lanes stride the entries, then a
+// butterfly: a fixed order.
+template <int T>
+__device__ void per_instance_sum(const double *buf, int m, int n2, double *out) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int b = wave; b < m; b += T / 64) {
+    double v = 0.0;
+    for (int e = lane; e < n2; e += 64) v += buf[b * n2 + e];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    if (lane == 0) out[b] = v;
+  }
+}
+
 // Expectation values of the instances whose out_due >= 0 (their rho is in Y).
 template <int T>
 __device__ void dp_outputs(const Dp5Args &a, const PackDesc &pk, const PackLds &L,
