@@ -31,17 +31,19 @@ METRIC = "instance-RK-steps/sec + HBM GB/s, batched vs plain, at 1e-10 trace dis
 # only while the kernel's source file has the SHA-256 recorded with them; any other
 # source reports null.
 TRAFFIC_SOURCES = {
-    "lme_kernels.hip": "5c1c6e4612d8bbb6f71a8e1cdcc9befa366c5c42b067f6889e915b74ae7e1d59",
-    "lme_mc.hip": "430556a8477c37b2518b1ef033bf9e5d02253ea52ef0d06223e0015092f8d385",
+    "lme_kernels.hip": "1be4ec872ae09c2c81b91eca2cff3339a4af15ae6de7371e0a110e2b8c7974c0",
+    "lme_band.hip": "8d2087f2d6be95ec9426c3217db6c8d36d3a712befc25eb2a451acacf82f8b66",
+    "lme_flip.hip": "2ca65ee2a84e2cbe060e2402de720ee109e4f06011df34613361e2fb8f65fcc0",
+    "lme_mc.hip": "097a01f6767e0efdb3e6054f8b618ddf8354c4022bae1838dcb588ae965e0b63",
     "lme_prop.hip": "1cb74cb326de73396be2810a8f7bc6a348ad3fa4957b14d9137df9ade952e57d",
 }
 TRAFFIC = {
-    "rk4_herm_kernel": ("lme_kernels.hip", 192.1e6 + 178.2e6),
-    "rk4_colown_kernel": ("lme_kernels.hip", 217.2e6 + 234.0e6),
-    "apply_pipe_kernel": ("lme_kernels.hip", 184.5e6 + 158.3e6),
-    "apply_rows_kernel": ("lme_kernels.hip", 154.7e6 + 104.9e6),
-    "mc_kernel": ("lme_mc.hip", 2332.6e6 + 3173.0e6),
-    "zgemm_kernel": ("lme_prop.hip", 2450.9e6 + 268.4e6),
+    "rk4_band_kernel": ("lme_band.hip", 202.9e6 + 191.2e6),
+    "rk4_colown_kernel": ("lme_kernels.hip", 217.2e6 + 233.9e6),
+    "apply_pipe_kernel": ("lme_kernels.hip", 184.4e6 + 158.3e6),
+    "apply_flip_kernel": ("lme_flip.hip", 104.1e6 + 67.1e6),
+    "mc_reg_kernel": ("lme_mc.hip", 4411.3e6 + 3956.3e6),
+    "zgemm_kernel": ("lme_prop.hip", 2460.5e6 + 268.4e6),
 }
 
 
@@ -92,11 +94,10 @@ def survey_apply_flops(s):
 
 
 def herm_lds_bytes_per_element_stage(s):
-    """LDS bytes one element-stage of the Hermitian resident kernel moves
-    (row data in registers): the y gathers of A y, y A^+ (one per
-    off-diagonal entry of A on each side) and C_k y C_k^+ (one per monomial
-    collapse operator), 16 bytes each, plus the stage input stored twice
-    (the element and its conjugate mirror)."""
+    """LDS bytes one element-stage of the resident Hermitian kernel for banded
+    operators moves (row neighbours and row data in registers): the y gathers
+    of y A^+ (one per off-diagonal entry of a row of A) and C_k y C_k^+ (one
+    per collapse operator) and the stored stage input, 16 bytes each."""
     import scipy.sparse as sp
     A = sp.csr_matrix(-1j * s.H0)
     for c in s.C:
@@ -105,7 +106,7 @@ def herm_lds_bytes_per_element_stage(s):
     A.setdiag(0)
     A.eliminate_zeros()
     wo = int(np.max(np.diff(A.indptr))) if A.nnz else 0
-    return 16.0 * (2 * wo + len(s.C)) + 32.0
+    return 16.0 * (wo + len(s.C) + 1)
 
 
 def lds_peak_tbs(lme, torch, reps=5):
@@ -284,7 +285,7 @@ def mc_trilinear_bench(lme, systems, torch, reps=3):
             "jumps_mean": float(jumps.mean()), "status_ok": bool((st == 0).all()),
             "algorithmic_flops": flops, "achieved_tflops": flops / (kms * 1e-3) / 1e12,
             "frac_fp64_peak": flops / (kms * 1e-3) / 1e12 / FP64_VECTOR_PEAK_TFLOPS,
-            "kernel": "mc_kernel", "traffic": kernel_traffic("mc_kernel")}
+            "kernel": "mc_reg_kernel", "traffic": kernel_traffic("mc_reg_kernel")}
 
 
 FP64_MFMA_PEAK_TFLOPS = 78.6
@@ -409,7 +410,7 @@ def tfim_apply_bench(lme, systems, torch, reps=10):
     """HBM roofline of the Liouvillian application on 8-spin chains (n = 256,
     1 MiB per state): 64 realizations (134 MB per application) and 512 (1.07
     GB, past the last-level cache).  Algorithmic bytes 32 n^2 per instance.
-    The default form runs the row-block kernel; the plain streamed kernel
+    The default form runs the spin-flip kernel; the plain streamed kernel
     (every gather from memory) and a device copy of the same bytes are timed
     beside it."""
     res = {}
@@ -445,9 +446,9 @@ def tfim_apply_bench(lme, systems, torch, reps=10):
             r[name] = {"us_per_apply": us, "GBs": gbs, "frac": gbs / HBM_PEAK_GBS}
         src = torch.empty_like(y)
         cus = timed(lambda: out.copy_(src))
-        r["row_blocks"]["kernel"] = "apply_rows_kernel"
+        r["row_blocks"]["kernel"] = "apply_flip_kernel"
         if n_inst == 64:
-            r["row_blocks"]["traffic"] = kernel_traffic("apply_rows_kernel")
+            r["row_blocks"]["traffic"] = kernel_traffic("apply_flip_kernel")
         r["device_copy"] = {"us": cus, "GBs": nbytes / (cus * 1e-6) / 1e9}
         r["row_blocks"]["frac_of_copy"] = cus / r["row_blocks"]["us_per_apply"]
         res[f"tfim_8spin_x{n_inst}"] = r
@@ -541,7 +542,7 @@ def pmc_pass(lme, systems, torch):
         rc = lme.load().lme_apply(h._h, form, 0, 0.0, None, lme._ptr(rho0), lme._ptr(out),
                                   lme._stream_ptr(None))
         assert rc == 0
-    # the row-block application on 64 8-spin chains
+    # the application on 64 8-spin chains (spin-flip kernel)
     wt = systems.tfim(n_inst=64)
     ht = lme.Handle(wt.systems)
     yt = ht.pack([s.rho0 for s in wt.systems], device="cuda:0")
@@ -724,8 +725,8 @@ def main():
                      if herm else
                      {"bound": "alu", "achieved": achieved, "peak": FP64_VECTOR_PEAK_TFLOPS,
                       "unit": "TFLOP/s", "frac": achieved / FP64_VECTOR_PEAK_TFLOPS}) | {
-                     "traffic": kernel_traffic("rk4_herm_kernel" if herm else "rk4_colown_kernel"),
-                     "kernel": "rk4_herm_kernel" if herm else "rk4_colown_kernel",
+                     "traffic": kernel_traffic("rk4_band_kernel" if herm else "rk4_colown_kernel"),
+                     "kernel": "rk4_band_kernel" if herm else "rk4_colown_kernel",
                      "kernel_ms": k_ms,
                      "flops": {"scope_table_count": survey_flops,
                                "achieved_tflops": survey_tflops, "peak": FP64_VECTOR_PEAK_TFLOPS,
