@@ -58,3 +58,41 @@ def test_two_level_batches_bitwise_row_kernel(n_inst, jumps, ctrl, form, off, n_
     assert (a["status"].cpu().numpy() == 0).all()
     for k in ("expect", "states", "rho", "counts", "status"):
         assert torch.equal(a[k], b[k]), k
+
+
+JUMPS["zero"] = [[0, 0], [0, 0]]
+
+
+@pytest.mark.parametrize("n_inst,jumps,ctrl,form,off", [
+    (1, [["zero"]], "z", "polynomial", True), (40, [["zero"], ["down"]], "z", "polynomial", True),
+    (1, [["zero"]], "", "none", True), (9, [["zero", "zero"]], "", "none", False),
+    (40, [["zero", "zero"], ["down", "zero"], ["zero", "flip"]], "xz", "segments", True),
+    (33, [["zero"], ["phase"]], "zx", "cosine", False),
+    (5, [["zero"] * 6], "y", "segments", True)])
+def test_two_level_batches_with_operators_without_entries(n_inst, jumps, ctrl, form, off):
+    """Collapse operators whose entries are all zero (a decay rate of zero in
+    a sweep), alone and beside ones with entries: the bits of the row kernel,
+    and where every operator is zero those of the batch without operators."""
+    rng = np.random.default_rng(n_inst)
+    systems = [two_level(rng, jumps[b % len(jumps)], ctrl, form, off, 2) for b in range(n_inst)]
+    for s in systems[1:]:
+        s.edges = systems[0].edges
+    h = lme.Handle(systems)
+    rho0 = h.pack([rng.normal(size=(2, 2)) + 1j * rng.normal(size=(2, 2)) for _ in range(n_inst)])
+    tl = np.linspace(0.0, 1.0, 11)
+
+    def run(h, **kw):
+        out = h.evolve(rho0, tl, nsteps=50, want_states=True, **kw)
+        torch.cuda.synchronize()
+        assert (out["status"].cpu().numpy() == 0).all()
+        return out
+
+    a = run(h)
+    others = [run(h, block=256, layout=lme.LME_LAYOUT_ROW)]
+    if all(set(j) == {"zero"} for j in jumps):
+        for s in systems:
+            s.C = []
+        others.append(run(lme.Handle(systems)))
+    for b in others:
+        for k in ("expect", "states", "rho", "counts"):
+            assert torch.equal(a[k], b[k]), k
