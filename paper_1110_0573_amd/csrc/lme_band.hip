@@ -159,7 +159,7 @@ __device__ __forceinline__ void band_pack(const Rk4Args &a, const PackDesc &pk, 
 #pragma unroll
   for (int k = 0; k < NC; ++k) {
     jv[k] = op.Jval[k * n + j].x;
-    aj[k] = at(0, j + a.band_off[k]);
+    aj[k] = at(0, j + band_offset(a.band_off[k], n));
   }
   double2 dsum[EPT];
   double odn[EPT], oup[EPT], p[EPT][NC];

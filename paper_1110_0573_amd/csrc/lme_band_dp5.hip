@@ -239,7 +239,7 @@ __device__ __forceinline__ void dp5_band_pack(const Dp5Args &a, const PackDesc &
 #pragma unroll
   for (int k = 0; k < NC; ++k) {
     jv[k] = op.Jval[k * n + j].x;
-    aj[k] = at(d0, j + a.band_off[k]);
+    aj[k] = at(d0, j + band_offset(a.band_off[k], n));
   }
   const uint32_t own = at(d0, j), aprev = at(d0 - 1, j), anext = at(dl + 1, j);
   uint32_t ar[NW], af[NW], al[NW];

@@ -124,6 +124,12 @@ LME_HD constexpr bool herm_slots(bool re, int32_t wo, int32_t nc, int32_t nb) {
   return re && nb == 0 && wo + nc <= 3;
 }
 
+// Offset of the column that a collapse operator on diagonal `off` reads in an
+// instance of dimension n.  An instance too small for that diagonal holds the
+// operator without entries: its zeros weigh the column itself, never memory of
+// another instance (which may hold an infinity).
+LME_HD inline int32_t band_offset(int32_t off, int32_t n) { return off > -n && off < n ? off : 0; }
+
 // Band kernel (lme_band.hip): LDS of one buffer of m instances, diagonals -1
 // to n/2 + 1 as rows of n elements; diagonals past the last that a pack's
 // threads may read (with zero coefficients) after the second buffer.

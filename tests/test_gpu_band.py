@@ -85,3 +85,36 @@ def test_band_kernel_diverging_neighbour():
     for b in (300, 302, 299, 303):
         ex, _ = oracle.rk4(systems[b], systems[b].rho0, tl, 120, store_states=True)
         assert np.max(np.abs(out["expect"].cpu().numpy()[b] - ex)) <= 1e-10
+
+
+def short_of_diagonals(n, offsets, two_sided, seed):
+    """band_system() where n may be too small for some of the diagonals: those
+    operators have no entries (a nine-photon loss at a cutoff of four)."""
+    s = band_system(n, [d if abs(d) < n else 0 for d in offsets], two_sided, seed)
+    s.C = [c if abs(d) < n else S.tidy(np.zeros((n, n))) for c, d in zip(s.C, offsets)]
+    return s
+
+
+@pytest.mark.parametrize("offsets,two_sided", [((1, 9), True), ((-1, -9), True),
+                                               ((9, 1), False), ((1, -30, 9), False)])
+def test_band_kernel_diagonals_beyond_an_instance(offsets, two_sided):
+    """Small instances without a diagonal that a large one has, packed beside
+    one that overflows: nothing of it reaches them."""
+    dims = (40,) + (4,) * 600 + (9,) * 5
+    systems = [short_of_diagonals(n, offsets, two_sided, b) for b, n in enumerate(dims)]
+    systems[301].H0 = S.tidy(systems[301].H0 * 1e9)
+    tl = np.linspace(0.0, 1.2, 3)
+    h = lme.Handle(systems)
+    rho0 = h.pack([s.rho0 for s in systems])
+    out = h.evolve(rho0, tl, nsteps=120, hermitian=True)
+    ref = h.evolve(rho0, tl, nsteps=120, layout=lme.LME_LAYOUT_ROW)
+    torch.cuda.synchronize()
+    status = out["status"].cpu().numpy()
+    assert status[301] == lme.LME_ENONFINITE
+    assert (np.delete(status, 301) == 0).all()
+    rho, want = h.unpack(out["rho"]), h.unpack(ref["rho"])
+    for b in range(len(dims)):
+        assert b == 301 or np.max(np.abs(rho[b] - want[b])) <= 1e-13, b
+    for b in (0, 1, 300, 302, len(dims) - 1):
+        ex, _ = oracle.rk4(systems[b], systems[b].rho0, tl, 120, store_states=True)
+        assert np.max(np.abs(out["expect"].cpu().numpy()[b] - ex)) <= 1e-10

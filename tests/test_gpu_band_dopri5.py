@@ -54,3 +54,26 @@ def test_band_dopri5_bits(dims, offsets, two_sided, h0):
         assert np.array_equal(got[k], ref[k]), k
     keep = slice(0, sum(n * n for n in dims[:-1]))
     assert np.array_equal(got["states"][:, keep], ref["states"][:, keep])
+
+
+@pytest.mark.parametrize("offsets,two_sided", [((1, 9), True), ((-1, -9), True),
+                                               ((9, 1), False), ((1, -30, 9), False)])
+def test_band_dopri5_diagonals_beyond_an_instance(offsets, two_sided):
+    """Small instances without a diagonal that a large one has, packed beside
+    one of infinities: the bits of the row kernel."""
+    dims = (40,) + (4,) * 600 + (9,) * 5
+    from tests.test_gpu_band import short_of_diagonals
+    systems = [short_of_diagonals(n, offsets, two_sided, b) for b, n in enumerate(dims)]
+    h = lme.Handle(systems)
+    rho0 = h.pack([np.full((4, 4), np.inf) if b == 301 else s.rho0
+                   for b, s in enumerate(systems)])
+    a, r = (h.evolve(rho0, np.linspace(0.0, 1.2, 3), method="dopri5", rtol=1e-7, atol=1e-9,
+                     layout=layout) for layout in (lme.LME_LAYOUT_AUTO, lme.LME_LAYOUT_ROW))
+    torch.cuda.synchronize()
+    status = a["status"].cpu().numpy()
+    assert status[301] == lme.LME_ENONFINITE and (np.delete(status, 301) == 0).all()
+    for k in ("status", "counts"):
+        assert torch.equal(a[k], r[k]), k
+    got, ref = h.unpack(a["rho"]), h.unpack(r["rho"])
+    for b in range(len(dims)):
+        assert b == 301 or np.array_equal(got[b], ref[b]), b
