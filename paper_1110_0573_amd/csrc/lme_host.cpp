@@ -667,12 +667,13 @@ static int ensure_device(lme_ctx *h) {
       (rc = h->d_fn.upload(h->fn.data(), h->fn.size() * sizeof(double), "closed-form amplitudes")))
     return rc;
   for (int adj = 0; adj < 2 && h->flip_logn > 0; ++adj) {
-    std::vector<double> &tab = h->flip_tab[adj];
+    const std::vector<double> &tab = h->flip_tab[adj];
     if ((rc = h->d_flip[adj].upload(tab.data(), tab.size() * sizeof(double), "spin-flip tables")))
       return rc;
     h->flip[adj].tab = static_cast<const double *>(h->d_flip[adj].p);
-    std::vector<double>().swap(tab);
   }
+  // every upload has succeeded: a call after a failed one would need the images
+  for (std::vector<double> &tab : h->flip_tab) std::vector<double>().swap(tab);
   h->on_device = true;
   return LME_OK;
 }
