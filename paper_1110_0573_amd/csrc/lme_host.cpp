@@ -1489,9 +1489,9 @@ static int evolve_dp5(lme_handle h, const lme_options *opt, int32_t n_t, const d
   const uint8_t *tb = static_cast<const uint8_t *>(h->d_stops.p);
   double *kbuf = static_cast<double *>(h->d_kbuf.p);
   if (noalloc) {
-    if ((rc = noalloc_stage(h, buf.data(), buf.size(), plan, (size_t)7 * h->state_elems * 16, s,
-                            &na)))
-      return rc;
+    // (the band kernel keeps its stage derivatives in registers)
+    const size_t kbytes = band ? 0 : (size_t)7 * h->state_elems * 16;
+    if ((rc = noalloc_stage(h, buf.data(), buf.size(), plan, kbytes, s, &na))) return rc;
     tb = na.base;
     kbuf = reinterpret_cast<double *>(na.base + na.kbuf_off);
   }

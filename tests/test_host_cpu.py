@@ -62,3 +62,25 @@ def test_spin_flip_tables_after_a_failed_upload(fake):
         name, _, _, _, tab = launches()[-1]
         assert "apply_flip_kernel" in name and int(tab, 16) != 0, (name, tab)
         """, FAKE_DEVICES="0")
+
+
+def test_noalloc_band_adaptive_needs_no_stage_derivatives(fake):
+    """lme_evolve_noalloc under banded operators: the kernel stores no stage
+    derivatives, so none of its scratch is asked for them (300 systems of 48
+    states would need 77 MB of 64).  Kernels that store them are still refused."""
+    run(fake, """
+        w = [S.kerr_system(48, 0.3, 0.2, 0.4, 0.5)] * 300
+        h = lme.Handle(w)
+        rho = np.zeros(h.state_elems, complex)
+        ex = np.zeros((300, 2, 2), complex)
+        tl = np.array([0.0, 1.0])
+
+        def noalloc(layout):
+            o = lme.default_options(method=lme.LME_DOPRI5, layout=layout)
+            return lib.lme_evolve_noalloc(h._h, C.byref(o), 2, tl.ctypes.data_as(lme._PD),
+                                          rho.ctypes.data, None, ex.ctypes.data, None,
+                                          rho.ctypes.data, None, None, None)
+        assert noalloc(lme.LME_LAYOUT_ROW) == lme.LME_ENOTSUP and not launches()
+        assert noalloc(lme.LME_LAYOUT_AUTO) == 0, lib.lme_last_error()
+        assert "dp5_band_kernel" in launches()[-1][0]
+        """)

@@ -95,3 +95,11 @@ def test_noalloc_rejects_what_does_not_fit():
         h2.evolve(h2.pack([s[0].rho0]), np.array([0.0, 1.0]), nsteps=10,
                   path=lme.LME_PATH_STREAMED, noalloc=True)
     assert e.value.code == lme.LME_ENOTSUP
+
+
+def test_noalloc_band_adaptive_beyond_stage_derivatives():
+    """Banded operators: a batch whose stage derivatives alone would exceed the
+    scratch array (the kernel keeps them in registers)."""
+    systems = [S.kerr_system(48, 0.3 + 0.002 * b, 0.2, 0.4, 0.5) for b in range(300)]
+    ref, got = both(systems, [0.0, 0.05, 0.1], method="dopri5", rtol=1e-6, atol=1e-9)
+    assert_same(ref, got)
