@@ -812,7 +812,9 @@ static int plan_packs(lme_ctx *h, int T, int EPT, int adjoint, int cap, int colu
       pk.wo = s.wo;
       pk.nb = s.nb;
       pk.wb = s.wb;
-      pk.nc = s.nc;
+      // operators without entries store no tables (the same layout): a kernel
+      // that takes one entry a row must not look for them
+      pk.nc = s.wc > 0 ? s.nc : 0;
       pk.wc = s.wc;
       pk.blob_bytes = blob;
       pk.lds_bytes = pack_lds(n, m, blob, s.nb);

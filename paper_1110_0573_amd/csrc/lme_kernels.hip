@@ -618,7 +618,6 @@ __device__ __forceinline__ void quad_pack(const Rk4Args &a, const PackDesc &pk, 
   // lanes past the pack have zero coefficients
   const bool own = tid < E;
   const int b = own ? tid / n2 : 0, r = tid & 3, i = r >> 1, j = r & 1;
-  const int nj = pk.wc ? pk.nc : 0;   // operators without entries have no tables
   const double2 zero = make_double2(0.0, 0.0);
   double2 dsum = zero, ao = zero, bo = zero, qd[NB ? NB : 1], qa[NB ? NB : 1], qb[NB ? NB : 1],
           jp[JT ? JT : 1];
@@ -656,7 +655,7 @@ __device__ __forceinline__ void quad_pack(const Rk4Args &a, const PackDesc &pk, 
     jp[t] = zero;
     jx[t] = -1;
     js[t] = tid;
-    if (t < nj) {
+    if (t < pk.nc) {
       int x = 0;
       if (own) {
         jp[t] = cmul(op.Jval[t * n + i], cconj(op.Jval[t * n + j]));
@@ -737,7 +736,7 @@ __device__ __forceinline__ void quad_pack(const Rk4Args &a, const PackDesc &pk, 
       }
 #pragma unroll
       for (int t = 0; t < JT; ++t)
-        if (NJ >= 0 || t < nj) {
+        if (NJ >= 0 || t < pk.nc) {
           double2 ys;
           if (NJ >= 0 || jx[t] == 3) ys = quad_read<3>(yn);
           else if (jx[t] == 0) ys = yn;
@@ -779,9 +778,8 @@ __global__ __launch_bounds__(64) void rk4_quad_kernel(Rk4Args a) {
   const int b = tid < 4 * pk.m ? tid / 4 : 0;
   const OpView op = make_view(L.blobs + (size_t)b * pk.blob_stride, BL);
   // what the pack's instances have in common (the same for every lane)
-  const int nj = pk.wc ? pk.nc : 0;
-  bool flips = nj <= 2;
-  for (int t = 0; t < nj; ++t)
+  bool flips = pk.nc <= 2;
+  for (int t = 0; t < pk.nc; ++t)
     for (int q = 0; q < n; ++q) {
       const double2 v = op.Jval[t * n + q];
       flips = flips && (op.Jcol[t * n + q] != q || (v.x == 0.0 && v.y == 0.0));
@@ -798,10 +796,10 @@ __global__ __launch_bounds__(64) void rk4_quad_kernel(Rk4Args a) {
     if (F == 2 || !flips) {
       if (co) quad_pack<NB, F, true, -1>(a, pk, L, op);
       else quad_pack<NB, F, false, -1>(a, pk, L, op);
-    } else if (nj == 0) {
+    } else if (pk.nc == 0) {
       if (co) quad_pack<NB, F, true, 0>(a, pk, L, op);
       else quad_pack<NB, F, false, 0>(a, pk, L, op);
-    } else if (nj == 1) {
+    } else if (pk.nc == 1) {
       if (co) quad_pack<NB, F, true, 1>(a, pk, L, op);
       else quad_pack<NB, F, false, 1>(a, pk, L, op);
     } else {
