@@ -333,11 +333,11 @@ __device__ __forceinline__ double2 lane_read(double2 v, int src) {
   return make_double2(__shfl(v.x, src, 64), __shfl(v.y, src, 64));
 }
 
-// Expectation values of a one-wavefront pack of small instances (n <= 8), one
-// (instance, operator) pair per lane: write_outputs() takes a wavefront per
-// pair, one after another (64 pairs of a Landau-Zener pack, most of a run
-// with an output every 20 steps).  A lane adds its rows in the order of the
-// butterfly, so the bits are those of write_outputs().
+// Expectation values of a one-wavefront pack of small instances (n <= 8):
+// write_outputs() takes a wavefront per (instance, operator) pair, one after
+// another (64 pairs of a Landau-Zener pack, most of a run with an output every
+// 20 steps).  Here a pair is one lane's or a few lanes' work, its rows added in
+// the order of write_outputs(): the same bits.
 struct LaneTask {
   const int32_t *Ec;
   const double2 *Ev;
@@ -361,27 +361,54 @@ __device__ __forceinline__ LaneTask lane_task(const Rk4Args &a, const PackDesc &
   return t;
 }
 
-// first: the pair of this lane in the first round (looked up once)
+__device__ __forceinline__ void put_output(const Rk4Args &a, const LaneTask &t, int k, double2 p) {
+  t.dst[2 * k] = p.x;
+  t.dst[2 * k + 1] = p.y;
+  if (!cfinite(p) && a.status) a.status[t.id] = 5;  // LME_ENONFINITE
+}
+
+// n = 2: one pair per lane.  first: the pair of this lane in the first round
+// (looked up once).
 __device__ __forceinline__ void lane_outputs(const Rk4Args &a, const PackDesc &pk,
                                              const PackLds &L, const LaneTask &first, int k) {
-  const int n = pk.n;
+  constexpr int n = 2;
   for (int task = threadIdx.x; task < pk.m * a.n_e; task += 64) {
     const LaneTask t = task < 64 ? first : lane_task(a, pk, L, task);
     const double2 *Y = L.Y + t.b * n * n;
-    double2 p[8];
+    double2 p[n];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < n; ++i) {
       p[i] = make_double2(0.0, 0.0);
-      if (i < n)
-        for (int w = 0; w < t.we; ++w) p[i] = cfma(t.Ev[w * n + i], Y[t.Ec[w * n + i] * n + i], p[i]);
+      for (int w = 0; w < t.we; ++w) p[i] = cfma(t.Ev[w * n + i], Y[t.Ec[w * n + i] * n + i], p[i]);
     }
-#pragma unroll
-    for (int off = 4; off > 0; off >>= 1)
-#pragma unroll
-      for (int i = 0; i < off; ++i) p[i] = cadd(p[i], p[i + off]);
-    t.dst[2 * k] = p[0].x;
-    t.dst[2 * k + 1] = p[0].y;
-    if (!cfinite(p[0]) && a.status) a.status[t.id] = 5;  // LME_ENONFINITE
+    put_output(a, t, k, cadd(p[0], p[1]));
+  }
+}
+
+// Any n <= 8: g >= n lanes per pair (a power of two), one row each.  201
+// outputs in 1000 steps, a dense operator of n = 8: 2.36 ms as with a wavefront
+// per pair; one pair per lane, up to 64 loads in turn, 3.50 ms.  Four diagonal
+// operators of n = 3: 2.23 ms; a wavefront per pair 2.58, a lane 2.35.
+__device__ __forceinline__ void row_outputs(const Rk4Args &a, const PackDesc &pk,
+                                            const PackLds &L, int k) {
+  // opaque copies: nothing derived from them is kept across the steps (30 more
+  // spilled scalar registers otherwise, 4 % of a step)
+  int n = pk.n, ntask = pk.m * a.n_e, tid = threadIdx.x;
+  asm volatile("" : "+s"(n), "+s"(ntask), "+v"(tid));
+  const int lg = n == 1 ? 0 : n == 2 ? 1 : n <= 4 ? 2 : 3, g = 1 << lg, i = tid & (g - 1);
+  for (int base = 0; base < ntask; base += 64 >> lg) {
+    const int task = base + (tid >> lg);
+    const LaneTask t = lane_task(a, pk, L, min(task, ntask - 1));
+    double2 p = make_double2(0.0, 0.0);
+    if (task < ntask && i < n) {
+      const double2 *Y = L.Y + t.b * n * n;
+      for (int w = 0; w < t.we; ++w) p = cfma(t.Ev[w * n + i], Y[t.Ec[w * n + i] * n + i], p);
+    }
+    for (int off = g >> 1; off > 0; off >>= 1) {
+      p.x += __shfl_xor(p.x, off, 64);
+      p.y += __shfl_xor(p.y, off, 64);
+    }
+    if (task < ntask && i == 0) put_output(a, t, k, p);
   }
 }
 
@@ -480,8 +507,6 @@ __global__ __launch_bounds__(64) void rk4_lane_kernel(Rk4Args a) {
   double2 rho = own ? reinterpret_cast<const double2 *>(a.rho0)[L.off[b] + r] : zero;
 
   const bool want_expect = a.expect != nullptr && a.n_e > 0;
-  LaneTask first = {};
-  if (want_expect && tid < pk.m * a.n_e) first = lane_task(a, pk, L, tid);
   int next_out = 0;
   const double h = a.h;
   for (int st = 0;; ++st) {
@@ -495,7 +520,7 @@ __global__ __launch_bounds__(64) void rk4_lane_kernel(Rk4Args a) {
               rho;
       }
       __syncthreads();
-      if (want_expect) lane_outputs(a, pk, L, first, next_out);
+      if (want_expect) row_outputs(a, pk, L, next_out);
       ++next_out;
     }
     if (st == a.nsteps) break;
