@@ -744,24 +744,23 @@ static int plan_packs(lme_ctx *h, int T, int EPT, int adjoint, int cap, int colu
     return lme_internal_pack_lds_bytes(n, m, blob, nb) +
            (dp == 1 ? lme_internal_dp5_extra_lds(m) : dp == 2 ? lme::align16(8 * m) : 0);
   };
-  // band kernel: a batch of few instances per CU is spread over the CUs, with
-  // fewer diagonals per thread, rather than packed (64 JC of n = 10 to 40,
-  // 1000 steps: 2.0 ms against 2.7)
   int cus = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess)
     cus = 0;
-  const int spread = column >= 4 && cus > 0 ? std::max(1, (h->n_inst + cus - 1) / cus) : h->n_inst;
-  for (auto &g : groups) {
-    const InstDesc &d0 = h->inst[g.second[0]];
+  auto blob_bytes = [&](const InstDesc &d) {
+    const lme::Signature &s = adjoint == 1 ? d.adj : d.fwd;
+    return column >= 4 ? 0
+           : column == 2 && lme::herm_slots(real_structure(h), s.wo, s.nc, s.nb) ? 0
+           : column >= 2 ? s.n * lme::rec_bytes(s.wo, s.nc, s.nb)
+           : adjoint == 1 ? d.adj_bytes
+           : adjoint == 2 ? d.fwd_bytes + d.adj_bytes : d.fwd_bytes;
+  };
+  // m instances per pack and G threads per column of a group of cnt instances
+  // like d0, at most `spread` of them in a pack (m < 1: not one fits)
+  auto shape = [&](const InstDesc &d0, int cnt, int spread, int *G_out) {
     const lme::Signature &s = adjoint == 1 ? d0.adj : d0.fwd;
-    const int blob = column >= 4 ? 0
-                     : column == 2 && lme::herm_slots(real_structure(h), s.wo, s.nc, s.nb) ? 0
-                     : column >= 2 ? s.n * lme::rec_bytes(s.wo, s.nc, s.nb)
-                     : adjoint == 1 ? d0.adj_bytes
-                     : adjoint == 2 ? d0.fwd_bytes + d0.adj_bytes : d0.fwd_bytes;
-    const int n = s.n;
+    const int blob = blob_bytes(d0), n = s.n;
     const int64_t n2 = (int64_t)n * n;
-    const int cnt = (int)g.second.size();
     // m instances that fit the LDS budget; an instance larger than the
     // budget alone gets the device limit
     auto lds_fit_in = [&](int64_t m, int64_t limit) {
@@ -779,24 +778,74 @@ static int plan_packs(lme_ctx *h, int T, int EPT, int adjoint, int cap, int colu
       const int r = lds_fit_in(m, budget);
       return (r > 0 || budget == h->lds_limit) ? r : lds_fit_in(std::min<int64_t>(m, 1), h->lds_limit);
     };
-    int m_max = 0, G = 0;
     const int R = column == 2 || column == 4 ? n / 2 + 1 : n;  // rows per column
-    if (!column) {
-      m_max = lds_fit(std::max<int64_t>(1, cap / n2));  // an instance larger than cap: alone
-    } else {
-      double best = -1.0;
-      for (int gg = (R + EPT - 1) / EPT; gg <= R && gg * n <= T; ++gg) {
-        const int ept = (R + gg - 1) / gg;
-        const int m = lds_fit(std::min<int64_t>(T / (gg * n), std::min(cnt, spread)));
-        if (m < 1) continue;
-        const double eff = (double)m * n * R / ((double)ept * T);
-        if (eff > best + 1e-12) {
-          best = eff;
-          m_max = m;
-          G = gg;
-        }
+    int m_max = 0;
+    *G_out = 0;
+    if (!column) return lds_fit(std::max<int64_t>(1, cap / n2));  // an instance larger than cap: alone
+    double best = -1.0;
+    for (int gg = (R + EPT - 1) / EPT; gg <= R && gg * n <= T; ++gg) {
+      const int ept = (R + gg - 1) / gg;
+      const int m = lds_fit(std::min<int64_t>(T / (gg * n), std::min(cnt, spread)));
+      if (m < 1) continue;
+      const double eff = (double)m * n * R / ((double)ept * T);
+      if (eff > best + 1e-12) {
+        best = eff;
+        m_max = m;
+        *G_out = gg;
       }
     }
+    return m_max;
+  };
+  // when the CUs, one workgroup at a time each, have worked through packs of
+  // the given rows per thread in their order, and the pack that ends last
+  auto schedule = [&](const std::vector<int> &ept, int *last) {
+    std::priority_queue<std::pair<int64_t, int>, std::vector<std::pair<int64_t, int>>,
+                        std::greater<std::pair<int64_t, int>>> free_at;
+    for (int c = 0; c < cus; ++c) free_at.push({0, c});
+    int64_t makespan = 0;
+    *last = -1;
+    for (int q = 0; q < (int)ept.size(); ++q) {
+      auto top = free_at.top();
+      free_at.pop();
+      const int64_t end = top.first + ept[q];
+      if (end >= makespan) {
+        makespan = end;
+        *last = q;
+      }
+      free_at.push({end, top.second});
+    }
+    return makespan;
+  };
+  // band kernels: a batch of few instances per CU is spread over the CUs, with
+  // fewer diagonals per thread, rather than packed (64 JC of n = 10 to 40,
+  // 1000 steps: 2.0 ms against 2.7), unless the smaller packs then take more
+  // rounds over the CUs than full ones (8192 JC of n = 10, 200 steps: 1.40 ms
+  // spread, 1.06 packed; 1024 of n = 20, 60 adaptive steps: 1.07 and 0.81)
+  int spread = h->n_inst;
+  if (column >= 4 && cus > 0) {
+    auto makespan = [&](int few) {
+      std::vector<int> ept;
+      int G = 0, last = 0;
+      for (auto &g : groups) {
+        const InstDesc &d0 = h->inst[g.second[0]];
+        const int cnt = (int)g.second.size(), m = shape(d0, cnt, few, &G);
+        const int R = column == 4 ? d0.n / 2 + 1 : d0.n;
+        if (m > 0) ept.insert(ept.end(), (cnt + m - 1) / m, (R + G - 1) / G);
+      }
+      std::sort(ept.begin(), ept.end(), std::greater<int>());
+      return schedule(ept, &last);
+    };
+    const int few = std::max(1, (h->n_inst + cus - 1) / cus);
+    if (makespan(few) <= makespan(h->n_inst)) spread = few;
+  }
+  for (auto &g : groups) {
+    const InstDesc &d0 = h->inst[g.second[0]];
+    const lme::Signature &s = adjoint == 1 ? d0.adj : d0.fwd;
+    const int blob = blob_bytes(d0);
+    const int n = s.n, cnt = (int)g.second.size();
+    const int R = column == 2 || column == 4 ? n / 2 + 1 : n;  // rows per column
+    int G = 0;
+    const int m_max = shape(d0, cnt, spread, &G);
     if (m_max < 1)
       return fail(LME_ENOTSUP, "instance of dimension %d does not fit a resident workgroup "
                   "(%s layout, %d B LDS available)", n, column ? "column" : "row", h->lds_limit);
@@ -849,21 +898,10 @@ static int plan_packs(lme_ctx *h, int T, int EPT, int adjoint, int cap, int colu
   // changes no result bit.
   if (column >= 1 && column != 3 && cus > 0) {
     for (int iter = 0; iter < 4 * cus; ++iter) {
-      std::priority_queue<std::pair<int64_t, int>, std::vector<std::pair<int64_t, int>>,
-                          std::greater<std::pair<int64_t, int>>> free_at;
-      for (int c = 0; c < cus; ++c) free_at.push({0, c});
-      int64_t makespan = 0;
+      std::vector<int> ept;
+      for (const PackDesc &q : p->packs) ept.push_back(q.ept);
       int last = -1;
-      for (int q = 0; q < (int)p->packs.size(); ++q) {
-        auto top = free_at.top();
-        free_at.pop();
-        const int64_t end = top.first + p->packs[q].ept;
-        if (end >= makespan) {
-          makespan = end;
-          last = q;
-        }
-        free_at.push({end, top.second});
-      }
+      schedule(ept, &last);
       if (last < 0) break;
       PackDesc pk = p->packs[last];
       if (pk.m < 2) break;

@@ -84,3 +84,22 @@ def test_noalloc_band_adaptive_needs_no_stage_derivatives(fake):
         assert noalloc(lme.LME_LAYOUT_AUTO) == 0, lib.lme_last_error()
         assert "dp5_band_kernel" in launches()[-1][0]
         """)
+
+
+@pytest.mark.parametrize("n_inst,method,N,spread", [
+    (8192, "LME_RK4", 5, False), (1024, "LME_RK4", 5, True), (1024, "LME_DOPRI5", 10, False),
+    (512, "LME_DOPRI5", 10, True)])
+def test_band_packs_rounds_over_the_cus(fake, n_inst, method, N, spread):
+    """A pack or more for each of the 256 CUs, but no second round over them
+    where full packs take less."""
+    run(fake, f"""
+        h = lme.Handle([S.jc_system({N})] * {n_inst})
+        rho = np.zeros(h.state_elems, complex)
+        ex = np.zeros(({n_inst}, 2, 2), complex)
+        tl = np.array([0.0, 1.0])
+        o = lme.default_options(method=lme.{method}, nsteps=10, hermitian=1)
+        assert lib.lme_evolve(h._h, C.byref(o), 2, tl.ctypes.data_as(lme._PD), rho.ctypes.data, None,
+                              ex.ctypes.data, None, rho.ctypes.data, None, None, None) == 0
+        name, grid = launches()[-1][:2]
+        assert "band_kernel" in name and (int(grid) >= 256) == {spread}, (name, grid)
+        """)
