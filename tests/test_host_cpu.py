@@ -86,12 +86,11 @@ def test_noalloc_band_adaptive_needs_no_stage_derivatives(fake):
         """)
 
 
-@pytest.mark.parametrize("n_inst,method,N,spread", [
-    (8192, "LME_RK4", 5, False), (1024, "LME_RK4", 5, True), (1024, "LME_DOPRI5", 10, False),
-    (512, "LME_DOPRI5", 10, True)])
-def test_band_packs_rounds_over_the_cus(fake, n_inst, method, N, spread):
-    """A pack or more for each of the 256 CUs, but no second round over them
-    where full packs take less."""
+@pytest.mark.parametrize("n_inst,method,N", [
+    (8192, "LME_RK4", 5), (1024, "LME_RK4", 5), (1024, "LME_DOPRI5", 10), (512, "LME_DOPRI5", 10)])
+def test_band_packs_rounds_over_the_cus(fake, n_inst, method, N):
+    """Packs for the 256 CUs, but no second round over them where full packs
+    take less (the last to end are split in two, for a few packs more)."""
     run(fake, f"""
         h = lme.Handle([S.jc_system({N})] * {n_inst})
         rho = np.zeros(h.state_elems, complex)
@@ -101,5 +100,5 @@ def test_band_packs_rounds_over_the_cus(fake, n_inst, method, N, spread):
         assert lib.lme_evolve(h._h, C.byref(o), 2, tl.ctypes.data_as(lme._PD), rho.ctypes.data, None,
                               ex.ctypes.data, None, rho.ctypes.data, None, None, None) == 0
         name, grid = launches()[-1][:2]
-        assert "band_kernel" in name and (int(grid) >= 256) == {spread}, (name, grid)
+        assert "band_kernel" in name and 200 <= int(grid) <= 260, (name, grid)
         """)
