@@ -118,3 +118,24 @@ def test_band_kernel_diagonals_beyond_an_instance(offsets, two_sided):
     for b in (0, 1, 300, 302, len(dims) - 1):
         ex, _ = oracle.rk4(systems[b], systems[b].rho0, tl, 120, store_states=True)
         assert np.max(np.abs(out["expect"].cpu().numpy()[b] - ex)) <= 1e-10
+
+
+@pytest.mark.parametrize("dims,offsets,two_sided", [
+    ((4, 5, 6, 7), (1, -1), True), ((4, 6, 8, 10), (2, 1), False), ((63, 64, 65), (1, -1), True),
+    ((72, 73), (2, -2, 1), False), ((81, 82, 83), (2, 1), False), ((82, 83), (1, -1), True),
+    ((20,) * 300, (2, 1), False)])
+def test_band_kernel_block_512(dims, offsets, two_sided):
+    """The 512-thread configuration (up to 7 diagonals a thread, n <= 83), which
+    runs where a caller names that block size: against the general path."""
+    systems = [band_system(n, offsets, two_sided, 100 * b + n) for b, n in enumerate(dims)]
+    tl = np.linspace(0.0, 1.2, 5)
+    h = lme.Handle(systems)
+    rho0 = h.pack([s.rho0 for s in systems])
+    out = h.evolve(rho0, tl, nsteps=120, hermitian=True, want_states=True, block=512,
+                   layout=lme.LME_LAYOUT_COLUMN)
+    ref = h.evolve(rho0, tl, nsteps=120, want_states=True)
+    torch.cuda.synchronize()
+    assert (out["status"].cpu().numpy() == 0).all()
+    assert torch.max(torch.abs(out["states"] - ref["states"])).item() <= 1e-13
+    for r in h.unpack(out["rho"]):
+        assert np.array_equal(r, r.conj().T)
