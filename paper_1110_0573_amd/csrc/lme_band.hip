@@ -29,7 +29,13 @@
 // polynomial and is evaluated by Horner's rule,
 //   x <- rho + h/k L x,   k = 4, 3, 2, 1, from x = rho,
 // which needs no running sum (20 registers a diagonal instead of 24; with the
-// sum the 768-thread configuration spills and takes 40.3 ms instead of 36.6).
+// sum the 768-thread configuration spills in its stages and takes 40.3 ms
+// instead of 36.6; as it is, 13 to 31 registers by operator shape spill, 7 to 17
+// reloads a step and none in a stage).  Rounding: the last stage's input enters
+// the result with h L, the classic form's three with h L / 3, / 3 and / 6.
+// Against an 80-bit RK4 the root mean square error is 1.1 to 1.7 times the
+// classic form's, the largest entry's 0.95 to 1.3 times (400 steps, n = 10 to
+// 40, 24 systems each: 0.7e-16 to 5.7e-16 of a trace of one).
 //
 // What bounds it (4096 Jaynes-Cummings instances of n = 10 to 80, 1000 steps:
 // 36.6 ms; rk4_herm_kernel, whose mirrored full matrix and per-lane rows cost

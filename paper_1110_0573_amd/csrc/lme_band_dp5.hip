@@ -23,10 +23,14 @@
 //     wavefronts that take step decisions save registers around it.
 // Bound by LDS reads (seven of 16 bytes an element and stage: 3640 cycles of a
 // stage at n = 60, 9 us of a step) and the latency that two or three wavefronts
-// a SIMD leave open, at n = 60 also by some twenty reloads of spilled registers
-// a stage.  One step of a driven Kerr system, dp5_resident_kernel's column form
-// -> here: n = 15 11.0 -> 4.4 us, n = 31 15.0 -> 7.8, n = 45 27.2 -> 13.1,
-// n = 60 38.5 -> 30.1.  At n = 60 a wavefront set aside for the decisions (448
+// a SIMD leave open, at n = 60 also by spilled registers (267 to 460 by operator
+// shape in eight diagonals a thread, about 25 reloads a stage; the column form
+// of 1024 threads 68 to 74).  One step of a driven Kerr system, dp5_resident_kernel's column
+// form -> here: n = 15 11.0 -> 4.4 us, n = 31 15.0 -> 7.8, n = 45 27.2 -> 13.1,
+// n = 60 38.5 -> 30.1.  Batches gain more, with three collapse operators as with
+// two (30 attempts, 512 systems of n = 60: Kerr 4.60 -> 2.66 ms, thermal
+// Jaynes-Cummings 4.52 -> 2.63; of n = 20 those 1.78 -> 0.77 in 60 attempts).
+// At n = 60 a wavefront set aside for the decisions (448
 // threads of 9 diagonals) takes 38.0 us; k1 partly in LDS changes nothing.
 #include "lme_device.h"
 #include "lme_internal.h"

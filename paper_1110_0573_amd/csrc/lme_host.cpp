@@ -1499,9 +1499,12 @@ static int evolve_dp5(lme_handle h, const lme_options *opt, int32_t n_t, const d
   }
   // banded operators: the band kernel where it holds every instance (n <= 64;
   // the same bits).  A step of one driven Kerr system, here / column kernel:
-  // n = 15 4.4 / 11.0 us, 31 7.8 / 15.0, 45 13.1 / 27.2, 60 30.1 / 38.5.  The
-  // first configuration serves n <= 48; beyond it a thread needs more
-  // diagonals than 768 threads have registers for.
+  // n = 15 4.4 / 11.0 us, 31 7.8 / 15.0, 45 13.1 / 27.2, 60 30.1 / 38.5.  Over 1
+  // to 2048 systems of n = 5 to 64 and ragged batches, two and three collapse
+  // operators, it takes 0.22 to 0.83 of the column kernel's time: closest for
+  // one system of n = 64 (33 / 40 us a step), 30 attempts of 512 thermal JC of
+  // n = 64 2.8 / 4.8 ms.  The first configuration serves n <= 48; beyond it a
+  // thread needs more diagonals than 768 threads have registers for.
   int dcfg = 0;
   while (dcfg < 2 && !column_fits(h, lme::kBandDpCfg[dcfg][0], lme::kBandDpCfg[dcfg][1], false))
     ++dcfg;
@@ -1672,9 +1675,12 @@ static int evolve_impl(lme_handle h, const lme_options *opt, int32_t n_t, const 
   // Hermitian states under banded operators: the band kernel wherever it
   // applies (1000 steps, ms, band kernel / column == 2: 4096 JC of n = 10 to
   // 80 36.6 / 43.8, one of n = 20 1.08 / 1.97, one of n = 80 5.8 / 5.9; 1024
-  // thermal JC of n = 32 5.3 / 10.9; 1024 Kerr of n = 41 7.7 / 19.3), its
-  // 768-thread configuration first (three wavefronts a SIMD: 36.6 against
-  // 42.1 for 512 threads of 7 diagonals, 38.0 for 1024 of 4, which spill)
+  // thermal JC of n = 32 5.3 / 10.9; 1024 Kerr of n = 41 7.7 / 19.3).  Its
+  // 768-thread configuration holds every dimension that the 512-thread one does
+  // and is the faster (three wavefronts a SIMD: 36.6 against 42.1 for 512 threads
+  // of 7 diagonals, 38.0 for 1024 of 4, which spill): the latter runs where a
+  // caller or the tuner names block 512 (column == 2 with 512 threads: 1.03 to
+  // 2.9 times its time, 1024 JC or Kerr of n = 10 to 80)
   if (column == 2 && h->band)
     for (int cc = 1; cc >= 0 && column == 2; --cc) {
       const int bT = lme::kBandCfg[cc][0], bE = lme::kBandCfg[cc][1];

@@ -703,8 +703,10 @@ __device__ __forceinline__ JumpState mc_jump(const McArgs &a, cplx *X, cplx *PS,
 // costs only its LDS gathers and one store.  The RK4 step is evaluated by Horner's rule,
 //   psi(s) = psi + s A (psi + s/2 A (psi + s/3 A (psi + s/4 A psi))),
 // so a row keeps psi and the current vector (8 registers) and no running
-// sum: ten rows fit the 256 registers of a 512-thread workgroup (five rows in
-// 1024 threads of 128 registers spill: 58.2 ms for the figures below).  psi
+// sum.  Seven rows fit the 256 registers of a 512-thread workgroup; from eight
+// on some spill (ten rows of two real entries: 56, about twenty reloads a step;
+// of two imaginary ones or under a complex diagonal: 86).  Five rows in 1024
+// threads of 128 registers spill more: 58.2 ms for the figures below.  psi
 // being in registers, the LDS that held it is the second buffer of the
 // current vector: one barrier per product.  The norm of the new psi costs
 // none of its own: its wave partials are published by the barrier that also

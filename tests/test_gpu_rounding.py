@@ -2,9 +2,10 @@
 than the general ones, against 80-bit references (numpy's long double).
 
 Bars.  Band kernel: per step it rounds each element of the state once, as the
-classic form does, and the rest of its rounding enters times h; both errors
-are sums of as many rounding errors of the same size, so the larger of the two
-stays within three times the other's (maxima over some hundreds of elements).
+classic form does; of the rest, its last stage's input enters the result with
+h L as a whole, the classic form's three with h L / 3, / 3 and / 6, one half
+of that in the root of the squares.  So its error stays within twice the
+other's, within three times for the largest of some hundreds of elements.
 Spin-flip kernel: fewer rounded terms an element than the plain streamed
 kernel (the diagonal operators are one factor), so its root mean square error
 does not exceed that one's."""
