@@ -31,19 +31,19 @@ METRIC = "instance-RK-steps/sec + HBM GB/s, batched vs plain, at 1e-10 trace dis
 # only while the kernel's source file has the SHA-256 recorded with them; any other
 # source reports null.
 TRAFFIC_SOURCES = {
-    "lme_kernels.hip": "1be4ec872ae09c2c81b91eca2cff3339a4af15ae6de7371e0a110e2b8c7974c0",
-    "lme_band.hip": "8d2087f2d6be95ec9426c3217db6c8d36d3a712befc25eb2a451acacf82f8b66",
+    "lme_kernels.hip": "f8cd8b7f3a464b93118de10643c1056403c5a87d6b6449fb6d1844aeb61d70c9",
+    "lme_band.hip": "8f8ee70a0f9560a7a1afd424e83c02e6c9394311d870797217cd5e8edec56ce9",
     "lme_flip.hip": "2ca65ee2a84e2cbe060e2402de720ee109e4f06011df34613361e2fb8f65fcc0",
-    "lme_mc.hip": "097a01f6767e0efdb3e6054f8b618ddf8354c4022bae1838dcb588ae965e0b63",
+    "lme_mc.hip": "c6efae9cfa043b9d3e617a61f06829729edc4fb1bef68f6d27d1f6dcfaf958af",
     "lme_prop.hip": "1cb74cb326de73396be2810a8f7bc6a348ad3fa4957b14d9137df9ade952e57d",
 }
 TRAFFIC = {
-    "rk4_band_kernel": ("lme_band.hip", 202.9e6 + 191.2e6),
+    "rk4_band_kernel": ("lme_band.hip", 203.3e6 + 191.2e6),
     "rk4_colown_kernel": ("lme_kernels.hip", 217.2e6 + 233.9e6),
-    "apply_pipe_kernel": ("lme_kernels.hip", 184.4e6 + 158.3e6),
-    "apply_flip_kernel": ("lme_flip.hip", 104.1e6 + 67.1e6),
-    "mc_reg_kernel": ("lme_mc.hip", 4411.3e6 + 3956.3e6),
-    "zgemm_kernel": ("lme_prop.hip", 2460.5e6 + 268.4e6),
+    "apply_pipe_kernel": ("lme_kernels.hip", 184.4e6 + 158.4e6),
+    "apply_flip_kernel": ("lme_flip.hip", 105.2e6 + 67.1e6),
+    "mc_reg_kernel": ("lme_mc.hip", 4407.1e6 + 3955.2e6),
+    "zgemm_kernel": ("lme_prop.hip", 2445.0e6 + 268.4e6),
 }
 
 
